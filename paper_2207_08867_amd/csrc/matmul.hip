@@ -812,14 +812,17 @@ static hipError_t mm_kinds(const MmArgs<T> &g, int64_t batches, const void *A, i
     if (a_mc && b_mc && !b_trans) return mm_launch<T, NC, true, true, false, true>(g, batches, A, B, C, s);
     return hipErrorInvalidValue;
   }
-  if (b_trans) {
-    // linear layer: plain input times MC weight stored [out][in]
-    if (!a_mc && b_mc) return mm_launch<T, NC, false, true, true>(g, batches, A, B, C, s);
-    return hipErrorInvalidValue;
+  if constexpr (NC > 1) {  // (one component: seq_kernel on every grid)
+    if (b_trans) {
+      // linear layer: plain input times MC weight stored [out][in]
+      if (!a_mc && b_mc) return mm_launch<T, NC, false, true, true>(g, batches, A, B, C, s);
+      return hipErrorInvalidValue;
+    }
+    if (a_mc && b_mc) return mm_launch<T, NC, true, true, false>(g, batches, A, B, C, s);
+    if (a_mc) return mm_launch<T, NC, true, false, false>(g, batches, A, B, C, s);
+    return mm_launch<T, NC, false, true, false>(g, batches, A, B, C, s);
   }
-  if (a_mc && b_mc) return mm_launch<T, NC, true, true, false>(g, batches, A, B, C, s);
-  if (a_mc) return mm_launch<T, NC, true, false, false>(g, batches, A, B, C, s);
-  return mm_launch<T, NC, false, true, false>(g, batches, A, B, C, s);
+  return hipErrorInvalidValue;
 }
 
 template <typename T>
@@ -858,7 +861,39 @@ static hipError_t mm_typed(const MmLaunch &L, hipStream_t s) {
   return mm_dispatch<T>(L.nc, g, L.B1 * L.B2, L.A, L.a_mc, L.B, L.b_mc, L.b_trans, L.prune, L.C, s);
 }
 
+// Grids of few wavefronts take the kernel of seq.hpp, which overlaps the steps of one
+// output's chain but needs more registers (3 or 4 wavefronts per SIMD at nc = 3): up to
+// how many blocks of 256 outputs per CU it is the faster one, by format, kind and nc.
+// Measured at K = 256 (time of mm_kernel over seq_kernel at 1, 2, 4 and 8 blocks per CU):
+//   MC x MC      f16 nc 2 1.9 1.6 1.2 1.0, nc 3 1.4 0.7; f32 nc 2 2.7 1.7 1.1 1.2, nc 3
+//                1.9 1.0 0.8, nc 4 2.1 1.1 1.1 0.9; f64 nc 2 1.9 1.5 1.1 1.0, nc 3 1.7 1.1 0.9
+//   MC, plain    f16 nc 2 1.1 1.0 1.0, nc 3 1.3 1.1 1.0 0.9, nc 4 1.4 1.2 1.1 1.1; f32 nc 2
+//                1.6 1.3 1.1 1.2, nc 3 1.3 0.9 0.9; f64 nc 2 1.5 1.3 1.2 1.1, nc 3 1.4 1.2 1.1 1.0
+//   MC-Linear    f16 nc 2 1.8 1.6 1.3 1.1, nc 3 2.0 1.6 1.2 0.9; f32 nc 2 1.6 1.1 1.4 1.2, nc 3
+//                1.4 1.1 0.9; f64 nc 2 1.7 1.5 1.4 1.3, nc 3 1.7 1.4 1.3 1.1
+// binary64 nc = 4 with an MC A spills there.  With one component (no Simple-Renorm test, two
+// operations per step) seq_kernel's 16-byte LDS reads win on every grid: 4096^2 x 256 f16
+// 2.0, f32 2.9, f64 1.9.
+static int seq_blocks_per_cu(const MmLaunch &L) {
+  static constexpr int both[3][3] = {{4, 1, 1}, {8, 1, 2}, {4, 2, 0}};   // [f16, f32, f64][nc 2, 3, 4]
+  static constexpr int one_a[3][3] = {{2, 3, 8}, {8, 1, 8}, {8, 6, 0}};  // plain B
+  static constexpr int one_b[3][3] = {{2, 3, 8}, {8, 1, 8}, {8, 6, 3}};  // plain A
+  static constexpr int linear[3][3] = {{8, 4, 4}, {8, 2, 8}, {8, 8, 8}};
+  const auto &t = L.b_trans ? linear : (L.a_mc && L.b_mc ? both : (L.a_mc ? one_a : one_b));
+  return t[L.dtype][L.nc - 2];
+}
+
+static bool seq_wanted(const MmLaunch &L) {
+  if (L.prune) return false;
+  if (L.nc == 1) return true;
+  if (L.K == 0) return false;
+  const int64_t blocks = ((L.M + 15) / 16) * ((L.N + 15) / 16);
+  return blocks <= (int64_t)256 * seq_blocks_per_cu(L) / (L.B1 * L.B2);
+}
+
 hipError_t launch_matmul_general(const MmLaunch &L, hipStream_t stream) {
+  if (seq_wanted(L))
+    return L.dtype == 0 ? launch_seq16(L, stream) : (L.dtype == 2 ? launch_seq64(L, stream) : launch_seq32(L, stream));
   if (L.dtype == 0) return mm_typed<_Float16>(L, stream);
   if (L.dtype == 2) return mm_typed<double>(L, stream);
   return mm_typed<float>(L, stream);

@@ -44,8 +44,17 @@ struct MmLaunch {
   int64_t y_plane = 0, y_ld = 0;
   double alpha = 1.0, beta = 1.0;
   int prune = 0;  // 1: the pruned MC x MC product (both operands MC, no epilogue)
+  // MC-Linear's weight gradient only: A stored [planes][K][M] (B plain, not transposed; a
+  // plain A too is allowed then); last: column N - 1 of B is not stored and holds ones,
+  // C is [nc][M][N - 1] and that column of the result goes to last, [nc][M].
+  int a_trans = 0;
+  void *last = nullptr;
 };
 hipError_t launch_matmul_general(const MmLaunch &L, hipStream_t stream);
+// The same products by the few-wavefront kernel (seq.hpp); not the pruned one.
+hipError_t launch_seq16(const MmLaunch &L, hipStream_t stream);
+hipError_t launch_seq32(const MmLaunch &L, hipStream_t stream);
+hipError_t launch_seq64(const MmLaunch &L, hipStream_t stream);
 
 // C[nc][M][N] = A x B.  b_trans: B is stored as [planes][N][K] (a linear layer's
 // weight) instead of [planes][K][N].  bias: [nc][N] MC bias added with Add-MCN, or
