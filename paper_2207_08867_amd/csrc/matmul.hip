@@ -55,6 +55,7 @@ struct Lane {
   static constexpr int NA = AMC ? NC : 1;
   static constexpr int NB = BMC ? NC : 1;
   static constexpr int NP = (AMC && BMC) ? NC : 1;
+  static constexpr bool PLAIN = !AMC && !BMC;  // terms of two plain factors (plain_term)
   using Ops = Operands<T, NA, NB, TM, TN, KT, BM, BN>;
   T acc[NP][TM][TN][NC];
 
@@ -227,6 +228,11 @@ struct Lane {
   __device__ __forceinline__ void first_terms(const Ops &o) {
     if constexpr (PRUNE) {
       prune_step<0, (1 << NP) - 1, TPS, true>(o);
+    } else if constexpr (PLAIN) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) plain_term<T, NC>(o.a[i][0], o.b[j][0], acc[0][i][j]);
     } else if constexpr (SPOL == SR_SUFFIX) {
 #pragma unroll
       for (int p = 0; p < NP; ++p)
@@ -275,7 +281,9 @@ struct Lane {
 #pragma unroll
           for (int j = 0; j < TN; ++j) {
             T t[NC], sum[NC], last;
-            if constexpr (!AMC) {
+            if constexpr (PLAIN) {
+              plain_term<T, NC>(o.a[i][0], o.b[j][0], t);
+            } else if constexpr (!AMC) {
               scaling_kept<T, NC, false, TPS>(o.b[j], o.a[i][0], t, last);
               bad |= kept_invalid_mask<T, NC, TPS, true>(t, last);
             } else if (TPS && p > 0) {
@@ -317,11 +325,15 @@ struct Lane {
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
               T h[NC + 1], t[NC];
-              if constexpr (AMC)
-                scaling_terms<T, NC>(o.a[i], BMC ? o.b[j][p] : o.b[j][0], h);
-              else
-                scaling_terms<T, NC>(o.b[j], o.a[i][0], h);
-              compact_nz<T, NC + 1, NC>(h, t);
+              if constexpr (PLAIN) {
+                plain_term<T, NC>(o.a[i][0], o.b[j][0], t);
+              } else {
+                if constexpr (AMC)
+                  scaling_terms<T, NC>(o.a[i], BMC ? o.b[j][p] : o.b[j][0], h);
+                else
+                  scaling_terms<T, NC>(o.b[j], o.a[i][0], h);
+                compact_nz<T, NC + 1, NC>(h, t);
+              }
               add_terms<T, NC>(acc[p][i][j], t, h);
               compact_nz<T, NC + 1, NC>(h, acc[p][i][j]);
             }
@@ -421,7 +433,10 @@ struct Lane {
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
           T term[NC];
-          if constexpr (!AMC) {
+          if constexpr (PLAIN) {
+            plain_term<T, NC>(o.a[i][0], o.b[j][0], term);
+            add_kept_into<false>(acc[p][i][j], term);
+          } else if constexpr (!AMC) {
             scale_kept<false, TPS>(o.b[j], o.a[i][0], term);
             add_kept_into<false>(acc[p][i][j], term);
           } else if (BMC && TPS && p > 0) {
@@ -449,11 +464,15 @@ struct Lane {
         for (int j = 0; j < TN; ++j) {
           const T v = AMC ? o.b[j][p] : o.a[i][0];
           T h[NC + 1], term[NC];
-          if constexpr (AMC)
-            scaling_terms<T, NC>(o.a[i], v, h);
-          else
-            scaling_terms<T, NC>(o.b[j], v, h);
-          if (__builtin_expect(sr_try<T, NC, SPOL>(h, term, v == T(0)), 0)) compact_nz<T, NC + 1, NC>(h, term);
+          if constexpr (PLAIN) {
+            plain_term<T, NC>(v, o.b[j][0], term);
+          } else {
+            if constexpr (AMC)
+              scaling_terms<T, NC>(o.a[i], v, h);
+            else
+              scaling_terms<T, NC>(o.b[j], v, h);
+            if (__builtin_expect(sr_try<T, NC, SPOL>(h, term, v == T(0)), 0)) compact_nz<T, NC + 1, NC>(h, term);
+          }
           add_terms<T, NC>(acc[p][i][j], term, h);
           if (__builtin_expect(sr_try<T, NC, APOL>(h, acc[p][i][j]), 0)) compact_nz<T, NC + 1, NC>(h, acc[p][i][j]);
         }
@@ -606,7 +625,7 @@ mm_kernel(const T *__restrict__ A, const T *__restrict__ B,
   // (|a_c| < |a_{c+1}|, or a NaN); when none has and the products are exact, the
   // ScalingN terms of B's low components are exact products in magnitude order and
   // need no kept-terms test (ORD).
-  constexpr bool TRACK = SPOL == SR_SUFFIX && NC > 1;
+  constexpr bool TRACK = SPOL == SR_SUFFIX && NC > 1 && (AMC || BMC);
   constexpr bool ORD_OK = TRACK && AMC && BMC && !PRUNE;
   constexpr int NSLOT = NA + NB + (ORD_OK ? 1 : 0);
   __shared__ uint32_t mx[2][NSLOT];
@@ -756,8 +775,10 @@ static hipError_t mm_launch_tile(MmArgs<T> g, int64_t batches, const void *A, co
   for (int64_t b0 = 0; b0 < batches; b0 += MM_MAX_GRID_Y) {
     g.bb0 = b0;
     const int64_t nb = (batches - b0) < MM_MAX_GRID_Y ? (batches - b0) : MM_MAX_GRID_Y;
-    if (g.mode == 2)  // the AddMM epilogue is a separate instantiation: it needs more registers
-      hipLaunchKernelGGL((mm_kernel<T, NC, AMC, BMC, BT, TM, TN, KT, SPOL, APOL, false, true, PRUNE, DEPTH>),
+    // the AddMM epilogue is a separate instantiation: it needs more registers
+    constexpr bool ADDMM_OK = (AMC || BMC) && !BT && !PRUNE;
+    if (ADDMM_OK && g.mode == 2)
+      hipLaunchKernelGGL((mm_kernel<T, NC, AMC, BMC, BT, TM, TN, KT, SPOL, APOL, false, ADDMM_OK, PRUNE, DEPTH>),
                          dim3(gx, (unsigned)nb), dim3(MM_THREADS), 0, s, (const T *)A, (const T *)B, (T *)C, g);
     else
       hipLaunchKernelGGL((mm_kernel<T, NC, AMC, BMC, BT, TM, TN, KT, SPOL, APOL, false, false, PRUNE, DEPTH>),
@@ -820,7 +841,8 @@ static hipError_t mm_kinds(const MmArgs<T> &g, int64_t batches, const void *A, i
     }
     if (a_mc && b_mc) return mm_launch<T, NC, true, true, false>(g, batches, A, B, C, s);
     if (a_mc) return mm_launch<T, NC, true, false, false>(g, batches, A, B, C, s);
-    return mm_launch<T, NC, false, true, false>(g, batches, A, B, C, s);
+    if (b_mc) return mm_launch<T, NC, false, true, false>(g, batches, A, B, C, s);
+    return mm_launch<T, NC, false, false, false>(g, batches, A, B, C, s);  // (weight gradient of a plain dY)
   }
   return hipErrorInvalidValue;
 }
@@ -879,11 +901,12 @@ static int seq_blocks_per_cu(const MmLaunch &L) {
   static constexpr int one_a[3][3] = {{2, 3, 8}, {8, 1, 8}, {8, 6, 0}};  // plain B
   static constexpr int one_b[3][3] = {{2, 3, 8}, {8, 1, 8}, {8, 6, 3}};  // plain A
   static constexpr int linear[3][3] = {{8, 4, 4}, {8, 2, 8}, {8, 8, 8}};
+  if (!L.a_mc && !L.b_mc) return 8;  // two plain factors
   const auto &t = L.b_trans ? linear : (L.a_mc && L.b_mc ? both : (L.a_mc ? one_a : one_b));
   return t[L.dtype][L.nc - 2];
 }
 
-static bool seq_wanted(const MmLaunch &L) {
+bool seq_wanted(const MmLaunch &L) {
   if (L.prune) return false;
   if (L.nc == 1) return true;
   if (L.K == 0) return false;
@@ -891,9 +914,12 @@ static bool seq_wanted(const MmLaunch &L) {
   return blocks <= (int64_t)256 * seq_blocks_per_cu(L) / (L.B1 * L.B2);
 }
 
+hipError_t launch_seq(const MmLaunch &L, hipStream_t stream) {
+  return L.dtype == 0 ? launch_seq16(L, stream) : (L.dtype == 2 ? launch_seq64(L, stream) : launch_seq32(L, stream));
+}
+
 hipError_t launch_matmul_general(const MmLaunch &L, hipStream_t stream) {
-  if (seq_wanted(L))
-    return L.dtype == 0 ? launch_seq16(L, stream) : (L.dtype == 2 ? launch_seq64(L, stream) : launch_seq32(L, stream));
+  if (seq_wanted(L)) return launch_seq(L, stream);
   if (L.dtype == 0) return mm_typed<_Float16>(L, stream);
   if (L.dtype == 2) return mm_typed<double>(L, stream);
   return mm_typed<float>(L, stream);

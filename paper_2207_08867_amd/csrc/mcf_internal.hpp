@@ -44,14 +44,18 @@ struct MmLaunch {
   int64_t y_plane = 0, y_ld = 0;
   double alpha = 1.0, beta = 1.0;
   int prune = 0;  // 1: the pruned MC x MC product (both operands MC, no epilogue)
-  // MC-Linear's weight gradient only: A stored [planes][K][M] (B plain, not transposed; a
-  // plain A too is allowed then); last: column N - 1 of B is not stored and holds ones,
-  // C is [nc][M][N - 1] and that column of the result goes to last, [nc][M].
+  // MC-Linear's weight gradient also takes two plain operands (a_mc = b_mc = 0: the terms
+  // are their exact products) and, on grids for seq_wanted only, A stored [planes][K][M]
+  // (a_trans) and a last column N - 1 of B that is not stored and holds ones (`last`: C is
+  // [nc][M][N - 1] and that column of the result goes to last, [nc][M]).
   int a_trans = 0;
   void *last = nullptr;
 };
 hipError_t launch_matmul_general(const MmLaunch &L, hipStream_t stream);
-// The same products by the few-wavefront kernel (seq.hpp); not the pruned one.
+// Whether a product takes the few-wavefront kernel (seq.hpp), and that kernel's launch (any
+// grid; not the pruned product).
+bool seq_wanted(const MmLaunch &L);
+hipError_t launch_seq(const MmLaunch &L, hipStream_t stream);
 hipError_t launch_seq16(const MmLaunch &L, hipStream_t stream);
 hipError_t launch_seq32(const MmLaunch &L, hipStream_t stream);
 hipError_t launch_seq64(const MmLaunch &L, hipStream_t stream);

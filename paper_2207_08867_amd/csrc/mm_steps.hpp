@@ -148,6 +148,18 @@ __device__ __forceinline__ void add_terms(const T (&x)[N], const T (&y)[N], T (&
   h[N] = e;
 }
 
+// The term of two plain factors as an nc-component value: ScalingN of (x, 0, ..., 0) by v,
+// the exact product (p, e, 0, ...).  A zero p has a zero e (an underflowing product's
+// error rounds to zero), so Simple-Renorm would change nothing but zero signs.  The zeros
+// are -0: a sum with one is the other operand.
+template <typename T, int N>
+__device__ __forceinline__ void plain_term(T x, T v, T (&t)[N]) {
+  t[0] = x * v;
+  if constexpr (N > 1) t[1] = fma_(x, v, -t[0]);
+#pragma unroll
+  for (int c = 2; c < N; ++c) t[c] = -T(0);
+}
+
 // ---------------------------------------------------------------------------------
 // Kept-terms form of a step (policy SR_SUFFIX, used for binary16).
 //

@@ -106,10 +106,7 @@ struct SeqOps {
 template <typename T, int NC, int ROLE>
 __device__ __forceinline__ void seq_term_general(const T (&x)[ROLE == SEQ_PLAIN ? 1 : NC], T v, T (&t)[NC]) {
   if constexpr (ROLE == SEQ_PLAIN) {
-    t[0] = x[0] * v;
-    if constexpr (NC > 1) t[1] = fma_(x[0], v, -t[0]);
-#pragma unroll
-    for (int c = 2; c < NC; ++c) t[c] = T(0);
+    plain_term<T, NC>(x[0], v, t);
   } else {
     T h[NC + 1];
     scaling_terms<T, NC>(x, v, h);
@@ -320,18 +317,21 @@ seq_kernel(const SeqArgs<T> g) {
       } else {
         if (!strict) {
           bad = seq_group<T, NC, ROLE, U, false>(o, acc);
-          // (the wavefront stays with the other test: what failed is a property of its data)
-          strict = NC > 1 && __any(bad && valid);
-          if (__builtin_expect(!strict, 1)) return;
+          const bool again = NC > 1 && __any(bad && valid);
+          if (__builtin_expect(!again, 1)) return;
+          // The wavefront stays with the other test, since what failed is a property of
+          // its data; not so the first steps of plain factors, whose accumulator has no
+          // third component yet.
+          strict = ROLE != SEQ_PLAIN || k0 + kk > 0;
 #pragma unroll
           for (int c = 0; c < NC; ++c) acc[c] = saved[c];
         }
         // Operands read again, at a step the compiler cannot know: else it would keep the
         // terms of the first attempt in registers for this one.
-        int again = kk;
-        asm volatile("" : "+s"(again));
+        int at = kk;
+        asm volatile("" : "+s"(at));
         Ops o2;
-        read(o2, again);
+        read(o2, at);
         bad = seq_group<T, NC, ROLE, U, true>(o2, acc);
       }
       if (NC > 1 && __builtin_expect(bad && valid, 0)) {

@@ -78,3 +78,26 @@ def test_layer_shape_sampled(mcf, orc):
                                                                         cols=c), "dW")
     ones = np.ones((1, T, 1), dtype=np.float16)
     assert_bits(to_host(db), orc.matmul(Yt, ones, nc=nc, b_mc=False)[:, :, 0], "db")
+
+
+@pytest.mark.parametrize("dt", [np.float16, np.float32, np.float64])
+@pytest.mark.parametrize("nc", [1, 2, 3, 4])
+@pytest.mark.parametrize("T, I, O", [(19, 1036, 531), (130, 70, 33), (7, 64, 32)])
+def test_plain_gradient_paths(mcf, orc, dt, nc, T, I, O):
+    """dW and db of a plain dY: the large-grid kernel with its staging (more than 8 blocks
+    of 256 outputs per CU) and the few-wavefront one, over rows with zeros, exact products
+    and products that overflow."""
+    x, W, b = next(inputs.linear_inputs(T, I, O, nc, dt, seed=640 + nc))
+    dY = np.random.default_rng(650 + nc).normal(0, 0.5, (T, O)).astype(dt)
+    dY[:, 3] = 0
+    dY[1:, 5] = 0.5
+    dY[T // 2:, 7] = 0
+    dY[2, 9] = x[2, 11] = np.finfo(dt).max / 4
+    dY[0, 10] = np.inf
+    x[:, 13] = 0
+    got = mcf.mc_linear_bwd(to_dev(x), to_dev(W), to_dev(dY), dy_mc=False, dx=False)
+    want = orc.linear_bwd(x, W, dY, nc=nc, dy_mc=False)
+    assert_bits(to_host(got[1]), want[1], "dW")
+    assert_bits(to_host(got[2]), want[2], "db")
+    alone = mcf.mc_linear_bwd(to_dev(x), to_dev(W), to_dev(dY), dy_mc=False, dx=False, dw=False)
+    assert_bits(to_host(alone[2]), want[2], "db alone")
