@@ -155,7 +155,7 @@ __device__ __forceinline__ void add_terms(const T (&x)[N], const T (&y)[N], T (&
 template <typename T, int N>
 __device__ __forceinline__ void plain_term(T x, T v, T (&t)[N]) {
   t[0] = x * v;
-  if constexpr (N > 1) t[1] = fma_(x, v, -t[0]);
+  if constexpr (N > 1) t[1] = prod_err(x, v, t[0]);
 #pragma unroll
   for (int c = 2; c < N; ++c) t[c] = -T(0);
 }
@@ -216,7 +216,7 @@ __device__ __forceinline__ void scaling_kept(const T (&x)[N], T v, T (&h)[N], T 
   h[0] = x[0] * v;
   last = h[0];
   if constexpr (N == 1) return;
-  T e = HEAD_EXACT ? T(0) : fma_(x[0], v, -h[0]);
+  T e = HEAD_EXACT ? T(0) : prod_err(x[0], v, h[0]);
   bool carry_zero = HEAD_EXACT;
 #pragma unroll
   for (int i = 1; i < N; ++i) {
@@ -232,7 +232,7 @@ __device__ __forceinline__ void scaling_kept(const T (&x)[N], T v, T (&h)[N], T 
       if constexpr (TAIL_EXACT) {
         e = e2;
       } else {
-        e = fma_(x[i], v, -hp) + e2;
+        e = prod_err(x[i], v, hp) + e2;
       }
       carry_zero = false;
     }
