@@ -1,19 +1,27 @@
 // div_steps.hpp -- Div-MCN and Mult-MCN (A.2.1) as the elementwise kernels run them.
 //
 // They return exactly what div_mcn / mult_mcn of mcf_arith.hpp return, bit for bit,
-// with three shortcuts:
+// with four shortcuts:
 //   * each ScalingN(y, q) takes the kept-terms form of mm_steps.hpp (the nc terms
 //     Simple-Renorm keeps, no final carry, and a per-lane test that Simple-Renorm
 //     would not change them; failing lanes compute the full terms and compact them).
 //     A zero term of either sign may then reach the next Add-MCN where the literal
 //     step has +0; that only changes zero signs of that Add-MCN's Two-Sum errors,
 //     which Simple-Renorm drops, and its outputs are the same;
-//   * the last quotient digit q_nc is computed only by lanes where one of the digits
-//     q_0 .. q_{nc-1} is zero.  Simple-Renorm of the nc+1 digits keeps the first nc
-//     non-zero ones, so when those are all non-zero q_nc is never used;
+//   * the quotient digits share the reciprocal of the divisor's leading component
+//     (Divisor below);
+//   * the last quotient digit q_nc is computed only by lanes whose first digit is zero.
+//     The remainder is a Simple-Renorm output after the first update, so a later digit is
+//     zero only when the remainder is or when its quotient underflows, and then the update
+//     with it leaves the remainder as it is: zero digits trail, Simple-Renorm of the nc+1
+//     digits keeps the first nc as they are, and q_nc is not needed (it is zero whenever
+//     one of those is).  A divisor with infinite or NaN low components leaves the remainder's
+//     last component infinite or NaN: such lanes take the full algorithm too;
 //   * the remainder updates x - y q compact their terms by a shift (add_mcn_shift).
 // Measured on 2^26 elements at nc = 3 against the literal algorithm: binary16 Div-MCN
-// 514 -> 426 us and Mult-MCN 986 -> 824 us; binary32 562 -> 425 and 1112 -> 697 us.
+// 514 -> 215 us and Mult-MCN 986 -> 435 us; binary32 562 -> 424 and 1112 -> 500 us (at
+// about 5.5 TB/s; before the shared reciprocal, the digit test below and the short
+// Renormalize: 338, 734, 423 and 563 us).
 // The remainder updates x - y q cancel the leading component, so their terms usually
 // start with a zero and trail off in zeros; the shift compaction covers those
 // patterns (a simulation of the binary16 nc = 3 workload found no other pattern in
@@ -62,35 +70,117 @@ __device__ __forceinline__ void add_mcn_shift(const T (&x)[N], const T (&y)[N], 
   for (int i = 0; i < N; ++i) out[i] = z[0] ? h[i + 1] : h[i];
 }
 
+// Component divisions by one divisor.  General case: div_.
+template <typename T>
+struct Divisor {
+  T y;
+  __device__ __forceinline__ explicit Divisor(T y0) : y(y0) {}
+  __device__ __forceinline__ T divide(T a) const { return div_(a, y); }
+};
+
+// binary16 through binary32: q = a r with r within one unit in the last place of 1 / y,
+// then q + (a - y q) r.  The residual a - y q is exact (24-bit q and 11-bit y against an
+// a that nearly cancels), so the result is within 2^-24 (1 + 2^-20) |a / y| of a / y.  A
+// point halfway between two binary16 values is M 2^k with M < 2^12, and |a / y - M 2^k|,
+// if not zero, is at least 2^k / B for y = B 2^j, B < 2^11: more than 2^-23 |a / y|.  So no
+// halfway point lies between, and rounding to binary16 gives RN(a / y); a quotient that
+// is itself a halfway point (below the normal range) is a 12-bit binary32 value and
+// comes out exact.  Zero, infinite or NaN operands that matter make the residual a NaN.
+// 9 issue slots a quotient instead of 23 (binary32's division and the conversions).
+template <>
+struct Divisor<_Float16> {
+  _Float16 y;
+  float yf, r;
+  __device__ __forceinline__ explicit Divisor(_Float16 y0) : y(y0), yf((float)y0), r(__builtin_amdgcn_rcpf(yf)) {}
+  __device__ __forceinline__ _Float16 divide(_Float16 a) const {
+    const float af = (float)a;
+    float q = af * r;
+    q = __builtin_fmaf(__builtin_fmaf(-yf, q, af), r, q);
+    if (__builtin_expect(q != q, 0)) return div_(a, y);
+    return (_Float16)q;
+  }
+};
+
+// binary32: the steps the compiler expands an IEEE division to (reciprocal, one Newton
+// step on it, quotient, two residual corrections), without its scaling, which leaves
+// operands in this range as they are: 2^-20 < |y| < 2^20, 2^-80 < |q| < 2^40 (so
+// |a| > 2^-100: every residual is exact).  Outside it, and for zero, infinite or NaN
+// operands, div_.
+template <>
+struct Divisor<float> {
+  float y, r;
+  __device__ __forceinline__ explicit Divisor(float y0) : y(y0) {
+    const float r0 = __builtin_amdgcn_rcpf(y);
+    r = __builtin_fmaf(__builtin_fmaf(-y, r0, 1.0f), r0, r0);
+    const float m = __builtin_fabsf(y);
+    if (!(m > 0x1p-20f && m < 0x1p20f)) r = __builtin_nanf("");
+  }
+  __device__ __forceinline__ float divide(float a) const {
+    float q = a * r;
+    q = __builtin_fmaf(__builtin_fmaf(-y, q, a), r, q);
+    q = __builtin_fmaf(__builtin_fmaf(-y, q, a), r, q);
+    const float m = __builtin_fabsf(q);
+    if (__builtin_expect(!(m > 0x1p-80f && m < 0x1p40f), 0)) return div_(a, y);
+    return q;
+  }
+};
+
 template <typename T, int N>
 __device__ __forceinline__ void div_mcn_fast(const T (&x_in)[N], const T (&y)[N], T (&out)[N]) {
   T x[N];
 #pragma unroll
   for (int c = 0; c < N; ++c) x[c] = x_in[c];
   T h[N + 1];
-  T q = div_(x[0], y[0]);
+  const Divisor<T> by(y[0]);
+  T q = by.divide(x[0]);
   h[0] = q;
 #pragma unroll
   for (int i = 1; i <= N; ++i) {
-    if (i == N) {
-      bool all = true;
+    if (i == N && h[0] != T(0) && (N == 1 || finite_(x[N - 1]))) {
 #pragma unroll
-      for (int c = 0; c < N; ++c) all = all & (h[c] != T(0));
-      if (all) {
-#pragma unroll
-        for (int c = 0; c < N; ++c) out[c] = h[c];
-        return;
-      }
+      for (int c = 0; c < N; ++c) out[c] = h[c] + T(0);  // a zero digit leaves as +0, Simple-Renorm's padding
+      return;
     }
     T s[N], neg[N];
     scaling_n_kept<T, N>(y, q, s);
 #pragma unroll
     for (int c = 0; c < N; ++c) neg[c] = -s[c];
     add_mcn_shift<T, N>(x, neg, x);
-    q = div_(x[0], y[0]);
+    q = by.divide(x[0]);
     h[i] = q;
   }
   simple_renorm<T, N + 1, N>(h, out);
+}
+
+// Renormalize (Priest variant) of up to three components, what renormalize of mcf_arith.hpp
+// returns.  Its second sweep starts with Two-Sum(s, 0), which emits nothing when s is
+// finite, and at N = 2 goes on with Two-Sum(s, t_1) of a pair that a Two-Sum just
+// returned: the pair again.  What is left emits at most twice before the final s, so
+// the compaction is three selects.  (x + 0 makes the padding +0.)
+template <typename T, int N>
+__device__ __forceinline__ void renormalize_fast(const T (&x)[N], T (&b)[N]) {
+  if constexpr (N == 2 || N == 3) {
+    T s = x[0], t[N];
+#pragma unroll
+    for (int i = 1; i < N; ++i) two_sum(x[i], s, s, t[i]);
+    if (__builtin_expect(!finite_(s), 0)) {
+      renormalize<T, N, N>(x, b);
+    } else if constexpr (N == 2) {
+      b[0] = s;
+      b[1] = t[1] + T(0);
+    } else {
+      T s1, e1, s2, e2;
+      two_sum(s, t[1], s1, e1);
+      const bool emit = e1 != T(0);
+      two_sum(emit ? e1 : s1, t[2], s2, e2);
+      e2 = e2 + T(0);
+      b[0] = emit ? s1 : s2;
+      b[1] = emit ? s2 : e2;
+      b[2] = emit ? e2 : T(0);
+    }
+  } else {
+    renormalize<T, N, N>(x, b);
+  }
 }
 
 // Mult-MCN, fast version: Renormalize(Div-MCN(x, Renormalize(Div-MCN(1, y)))).
@@ -101,9 +191,9 @@ __device__ __forceinline__ void mult_mcn_fast(const T (&x)[N], const T (&y)[N], 
 #pragma unroll
   for (int c = 1; c < N; ++c) one[c] = T(0);
   div_mcn_fast<T, N>(one, y, q);
-  renormalize<T, N, N>(q, yinv);
+  renormalize_fast<T, N>(q, yinv);
   div_mcn_fast<T, N>(x, yinv, q);
-  renormalize<T, N, N>(q, out);
+  renormalize_fast<T, N>(q, out);
 }
 
 // Mult-MCN-Slow (mcf_arith.hpp: mult_mcn_slow) with its DivN steps taken by

@@ -5,7 +5,7 @@
 // Data are component-major planes; each thread moves 16 bytes per plane per step
 // (8 binary16 or 4 binary32 elements) with dwordx4 loads and stores, so one wave
 // reads 1 KiB contiguous per plane: fully coalesced HBM streams (the few longest
-// per-element algorithms take one element per lane: see ew_one_per_lane).  The arithmetic of
+// per-element algorithms take one element per lane: see ew_width).  The arithmetic of
 // each element is the per-element algorithm of mcf_arith.hpp (Div-MCN and Mult-MCN
 // through div_steps.hpp, which returns the same bits with fewer operations).
 #include <hip/hip_runtime.h>
@@ -192,21 +192,23 @@ static int ew_blocks(int64_t work) {
   return (int)b;
 }
 
-// Instantiations whose per-element body is so long that the compiler does not unroll
-// the loop over a 16-byte chunk's elements: their operand and result packs, indexed by
-// the loop counter, would live in scratch memory (binary16 Mult-MCN-Slow at nc = 3
-// moved 2.7 GB of it per 2^26 elements, mostly in cache: the steady-state time is 1%
-// lower without it).  They take one element per lane and plane instead.
+// Elements per lane and plane: 16 bytes, but one for instantiations whose per-element body
+// is so long that the compiler does not unroll the loop over a chunk's elements: their
+// operand and result packs, indexed by the loop counter, would live in scratch memory.
+// They are VALU-bound, so the narrower accesses cost nothing (binary16 nc = 3 Mult-MCN of
+// 2^22 / 2^26 elements: 1 a lane 33.5 / 435 us, 2 35.0 / 434, 4 38.0 / 433, 8 58.2 / 640;
+// Mult-MCN-Slow 56.5 / 758, 58.7 / 762, 63.5 / 762, 82.7 / 808).
 template <typename T, int NC, int OP, bool XMC, bool YMC>
-constexpr bool ew_one_per_lane() {
-  if constexpr (OP == EW_MUL_SLOW) return sizeof(T) == 2 ? NC >= 3 : (sizeof(T) == 4 && NC >= 4);
-  if constexpr (OP == EW_MUL && XMC && YMC) return sizeof(T) == 2 && NC >= 4;
-  return false;
+constexpr int ew_width() {
+  constexpr bool mult = OP == EW_MUL && XMC && YMC;
+  if constexpr (sizeof(T) == 2 && NC >= 3 && (mult || OP == EW_MUL_SLOW)) return 1;
+  if constexpr (sizeof(T) == 4 && NC >= 4 && OP == EW_MUL_SLOW) return 1;
+  return 16 / (int)sizeof(T);
 }
 
 template <typename T, int NC, int OP, bool XMC, bool YMC, int NCOUT>
 static hipError_t ew_launch(int64_t n, const void *x, const void *y, void *out, hipStream_t s) {
-  constexpr int W = ew_one_per_lane<T, NC, OP, XMC, YMC>() ? 1 : 16 / sizeof(T);
+  constexpr int W = ew_width<T, NC, OP, XMC, YMC>();
   constexpr int VB = W * (int)sizeof(T);
   const T *xp = (const T *)x;
   const T *yp = (const T *)y;

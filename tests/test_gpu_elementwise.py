@@ -300,3 +300,36 @@ def test_div_mult_unordered_components(mcf, orc, dt, nc, op):
         got = to_host(fn[0](to_dev(x), to_dev(y), nc=nc))
         want = fn[1](x, y, nc=nc)
     assert_bits(got, want, f"{op} unordered {dt.__name__} nc={nc}")
+
+
+@pytest.mark.parametrize("dt", [np.float16, np.float32, np.float64])
+@pytest.mark.parametrize("nc", [1, 2, 3, 4])
+@pytest.mark.parametrize("op", ["div", "mul", "mul_slow"])
+def test_div_range_edges(mcf, orc, dt, nc, op):
+    """Quotient digits through the shared reciprocal and past its range: leading divisor
+    components around 2^-20, 1 and 2^20, quotients around 2^-80, 1 and 2^40 and at both ends of
+    the format, exact and halfway quotients, vanishing remainders, subnormal, zero, infinite
+    and NaN components, also as low components and behind a zero."""
+    g = np.random.default_rng(700 + nc)
+    n = 40001
+    info = np.finfo(dt)
+    lo, hi = (info.minexp - info.nmant, info.maxexp - 1)
+
+    def side(centres, spread):
+        e = np.clip(g.choice(centres, n) + g.integers(-spread, spread + 1, n), lo, hi)
+        x = np.zeros((nc, n))
+        x[0] = np.ldexp(np.where(g.random(n) < 0.2, 1.0, 1.0 + g.random(n)), e) * g.choice([-1, 1], n)
+        for c in range(1, nc):
+            x[c] = x[c - 1] * np.ldexp(g.uniform(-1, 1, n), -(info.nmant + 1)) * (g.random(n) < 0.8)
+        x = x.astype(dt)
+        for value in (0.0, np.inf, -np.inf, np.nan, info.max, info.smallest_subnormal):
+            for c in range(nc):
+                x[c][g.random(n) < 0.004] = value
+        return x
+
+    with np.errstate(over="ignore", under="ignore", invalid="ignore"):
+        y = side([-20, 0, 0, 20, lo + 2, hi], 2)
+        x = side([-100, -60, -40, 0, 0, 20, 60, lo + 2, hi], 3)
+        x[:, ::7] = y[:, ::7] * dt(1.5)  # exact first digits
+    got = to_host(getattr(mcf, "mc_" + op)(to_dev(x), to_dev(y), nc=nc))
+    assert_bits(got, getattr(orc, op)(x, y, nc=nc), f"{op} {dt.__name__} nc={nc}")
