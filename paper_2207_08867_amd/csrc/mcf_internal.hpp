@@ -80,6 +80,11 @@ void splitk_shape(int64_t S, int *KS, int *G);
 int64_t splitk_roots(int64_t S);
 hipError_t launch_matmul_splitk(int dtype, int nc, int64_t M, int64_t N, int64_t K, const void *A, int a_mc,
                                 const void *B, int b_mc, int64_t S, void *W, void *C, hipStream_t stream);
+// The sums of one linear-regression step (splitk.hip): C [nc][d + nc] = the K-split products,
+// S <= 256 slices, of the MC residual R [nc][n] with the d columns of X [n][d] and with its
+// own nc components.
+hipError_t launch_linreg_sums(int dtype, int nc, int64_t n, int64_t d, const void *X, const void *R, int64_t S, void *C,
+                              hipStream_t stream);
 // Size of the static per-device scratch that mc_matmul_splitk_noalloc uses in place of
 // a workspace, and its device address on the device of `stream` (looked up once per
 // device).

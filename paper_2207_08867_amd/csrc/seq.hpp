@@ -157,6 +157,50 @@ __device__ __forceinline__ bool seq_group(const SeqOps<T, NC, ROLE, U> &o, T (&a
   return low.zero();
 }
 
+// U steps into acc: the straight line, then the general algorithm for lanes that fail.
+// again(o2) reads the operands again (binary32 and binary64, for the strict test), from
+// somewhere the compiler cannot know, or it would keep the terms of the first attempt in
+// registers; one(u, x, v) reads those of step u.  strict: the wavefront's state; valid:
+// the lane's result is wanted; first: these are the first steps of the reduction.
+template <typename T, int NC, int ROLE, int U, typename Again, typename One>
+__device__ __forceinline__ void seq_steps(const SeqOps<T, NC, ROLE, U> &o, T (&acc)[NC], bool &strict, bool valid,
+                                          bool first, const Again &again, const One &one) {
+  constexpr int NX = SeqOps<T, NC, ROLE, U>::NX;
+  T saved[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) saved[c] = acc[c];
+  bool bad;
+  if constexpr (sizeof(T) == 2) {
+    bad = seq_group<T, NC, ROLE, U, true>(o, acc);
+  } else {
+    if (!strict) {
+      bad = seq_group<T, NC, ROLE, U, false>(o, acc);
+      if (__builtin_expect(NC == 1 || !__any(bad && valid), 1)) return;
+      // The wavefront stays with the other test, since what failed is a property of its
+      // data; not so the first steps of plain factors, whose accumulator has no third
+      // component yet.
+      strict = ROLE != SEQ_PLAIN || !first;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) acc[c] = saved[c];
+    }
+    SeqOps<T, NC, ROLE, U> o2;
+    again(o2);
+    bad = seq_group<T, NC, ROLE, U, true>(o2, acc);
+  }
+  if (NC > 1 && __builtin_expect(bad && valid, 0)) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[c] = saved[c];
+#pragma unroll 1
+    for (int u = 0; u < U; ++u) {
+      T x[NX], v, t[NC], h[NC + 1];
+      one(u, x, v);
+      seq_term_general<T, NC, ROLE>(x, v, t);
+      add_terms<T, NC>(acc, t, h);
+      compact_nz<T, NC + 1, NC>(h, acc);
+    }
+  }
+}
+
 // One lane's piece of a plane's tile: 16 bytes along the contiguous dimension of an
 // operand stored [rows][K] (KC) or [K][rows].
 template <typename T, bool KC>
@@ -294,7 +338,7 @@ seq_kernel(const SeqArgs<T> g) {
   }
   __syncthreads();
   int buf = 0;
-  [[maybe_unused]] bool strict = false;
+  bool strict = false;
   for (int64_t k0 = 0; k0 < K; k0 += KT, buf ^= 1) {
     const bool more = k0 + KT < K;
     if (more) fetch(k0 + KT);
@@ -308,46 +352,19 @@ seq_kernel(const SeqArgs<T> g) {
       seq_read<T, U>(at + vs, o.v);
     };
     auto steps = [&](const Ops &o, int kk) {
-      T saved[NC];
+      seq_steps<T, NC, ROLE, U>(
+          o, acc, strict, valid, k0 + kk == 0,
+          [&](Ops &o2) {
+            int at = kk;
+            asm volatile("" : "+s"(at));
+            read(o2, at);
+          },
+          [&](int u, T(&x)[NX], T &v) {
+            const char *at = from + (kk + u) * (int)sizeof(T);
 #pragma unroll
-      for (int c = 0; c < NC; ++c) saved[c] = acc[c];
-      bool bad;
-      if constexpr (sizeof(T) == 2) {
-        bad = seq_group<T, NC, ROLE, U, true>(o, acc);
-      } else {
-        if (!strict) {
-          bad = seq_group<T, NC, ROLE, U, false>(o, acc);
-          const bool again = NC > 1 && __any(bad && valid);
-          if (__builtin_expect(!again, 1)) return;
-          // The wavefront stays with the other test, since what failed is a property of
-          // its data; not so the first steps of plain factors, whose accumulator has no
-          // third component yet.
-          strict = ROLE != SEQ_PLAIN || k0 + kk > 0;
-#pragma unroll
-          for (int c = 0; c < NC; ++c) acc[c] = saved[c];
-        }
-        // Operands read again, at a step the compiler cannot know: else it would keep the
-        // terms of the first attempt in registers for this one.
-        int at = kk;
-        asm volatile("" : "+s"(at));
-        Ops o2;
-        read(o2, at);
-        bad = seq_group<T, NC, ROLE, U, true>(o2, acc);
-      }
-      if (NC > 1 && __builtin_expect(bad && valid, 0)) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) acc[c] = saved[c];
-#pragma unroll 1
-        for (int u = 0; u < U; ++u) {
-          const char *at = from + (kk + u) * (int)sizeof(T);
-          T x[NX], t[NC], h[NC + 1];
-#pragma unroll
-          for (int c = 0; c < NX; ++c) x[c] = *reinterpret_cast<const T *>(at + xs + c * x_step);
-          seq_term_general<T, NC, ROLE>(x, *reinterpret_cast<const T *>(at + vs), t);
-          add_terms<T, NC>(acc, t, h);
-          compact_nz<T, NC + 1, NC>(h, acc);
-        }
-      }
+            for (int c = 0; c < NX; ++c) x[c] = *reinterpret_cast<const T *>(at + xs + c * x_step);
+            v = *reinterpret_cast<const T *>(at + vs);
+          });
     };
     // steps beyond K multiply zeros and leave the accumulator as it is
     Ops o0, o1;

@@ -30,6 +30,7 @@
 #include "mcf_arith.hpp"
 #include "mcf_internal.hpp"
 #include "mm_steps.hpp"
+#include "seq.hpp"
 
 namespace mcf {
 
@@ -191,6 +192,112 @@ __global__ __launch_bounds__(SK_THREADS) void sk_kernel(const T *__restrict__ A,
   }
 }
 
+// Phase 1 for few wavefronts, where a slice's chain of dependent steps sets the time (16 us
+// for the 64 steps of a binary32 nc = 2 reduction over 10000 values, whatever else the
+// chip does): U steps at a time as one straight line (seq.hpp), the next U steps' loads
+// in flight meanwhile, and for MC x MC 256 lanes for each component of B (np), whose
+// products are combined at the end.  The same slices, tree and results.
+// Columns from N1 on are not in B but in B2, a column after the other.
+template <typename T, int NC, int ROLE>
+__global__ __attribute__((amdgpu_flat_work_group_size(SK_THREADS, ROLE == SEQ_AMC ? SK_THREADS * NC : SK_THREADS)))
+void sk_chain_kernel(const T *__restrict__ A, const T *__restrict__ B, T *__restrict__ C, T *__restrict__ W, int64_t M,
+                     int64_t N, int64_t K, int64_t S, int KS, int G, int np, const T *__restrict__ B2, int64_t N1) {
+  constexpr int U = seq_unroll<T, NC>();
+  extern __shared__ __align__(16) char chain_lds[];
+  T(*lds)[NC] = reinterpret_cast<T(*)[NC]>(chain_lds);
+
+  const int64_t MN = M * N;
+  const int lane = threadIdx.x & (SK_THREADS - 1), p = threadIdx.x / SK_THREADS;
+  const int q = lane & (KS - 1);
+  const int64_t o = (int64_t)blockIdx.x * (SK_THREADS / KS) + lane / KS;
+  const int64_t s = (int64_t)blockIdx.y * KS + q;
+  const bool valid = o < MN && s < S;
+
+  T acc[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) acc[c] = T(0);
+  if (valid) {
+    const int64_t i = o / N, j = o - i * N;
+    const int64_t bn = j < N1 ? N1 : 1;
+    const T *Ai = A + i * K, *Bj = (j < N1 ? B + j : B2 + (j - N1) * K) + (ROLE == SEQ_AMC ? p * K * N1 : 0);
+    const T *xs = ROLE == SEQ_AMC ? Ai : Bj, *vs = ROLE == SEQ_AMC ? Bj : Ai;
+    const int64_t xk = ROLE == SEQ_AMC ? 1 : bn, vk = ROLE == SEQ_AMC ? bn : 1;
+    const int64_t x_plane = ROLE == SEQ_AMC ? M * K : K * N1;
+    using Ops = SeqOps<T, NC, ROLE, U>;
+    // steps beyond K are zeros, which leave the accumulator as it is
+    auto one = [&](int64_t k, T(&x)[NC], T &v) {
+      const bool in = k < K;
+      const int64_t kk = in ? k : 0;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        x[c] = xs[c * x_plane + kk * xk];
+        x[c] = in ? x[c] : T(0);
+      }
+      v = vs[kk * vk];
+      v = in ? v : T(0);
+    };
+    auto read = [&](Ops &ops, int64_t k) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        T x[NC];
+        one(k + u * S, x, ops.v[u]);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) ops.x[c][u] = x[c];
+      }
+    };
+    bool strict = false;
+    auto steps = [&](const Ops &ops, int64_t k) {
+      seq_steps<T, NC, ROLE, U>(
+          ops, acc, strict, true, k == s,
+          [&](Ops &o2) {
+            int64_t at = k;
+            asm volatile("" : "+v"(at));
+            read(o2, at);
+          },
+          [&](int u, T(&x)[NC], T &v) { one(k + u * S, x, v); });
+    };
+    Ops o0, o1;
+    read(o0, s);
+    for (int64_t k = s; k < K; k += 2 * U * S) {
+      read(o1, k + U * S);
+      steps(o0, k);
+      if (k + U * S >= K) break;
+      read(o0, k + 2 * U * S);
+      steps(o1, k + U * S);
+    }
+  }
+
+  constexpr int APOL = sizeof(T) >= 4 ? SR_FULL : SR_SELECT;
+  const int64_t left = S - (int64_t)blockIdx.y * KS;
+  const int count = left < KS ? (int)left : KS;
+  T(&acc1)[1][NC] = *reinterpret_cast<T(*)[1][NC]>(&acc);
+  group_tree<T, NC, 1, APOL>(acc1, q, KS, count, lds);
+
+  if (G > 1) {
+    if (q == 0 && o < MN) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) W[(((int64_t)blockIdx.y * np + p) * NC + c) * MN + o] = acc[c];
+    }
+    return;
+  }
+  if (np > 1) {
+    if (q == 0 && p > 0) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) lds[threadIdx.x][c] = acc[c];
+    }
+    __syncthreads();
+  }
+  if (q == 0 && p == 0 && o < MN) {
+    for (int r = 1; r < np; ++r) {
+      T part[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) part[c] = lds[r * SK_THREADS + lane][c];
+      mm_add<T, NC, APOL>(acc, part, acc);
+    }
+    sk_store<T, NC, 1, APOL>(acc1, C, MN, o);
+  }
+}
+
 // Phase 2: the tree levels above the G group roots of each output in W, in one launch.
 // Lane q of an output's GW-lane group takes roots q R .. q R + R - 1 (those below G)
 // and folds them in tree order in registers: entry j is pushed after one Add-MCN with
@@ -302,6 +409,26 @@ static void sk_reduce_launch(const T *W, T *C, int64_t MN, int G, hipStream_t s)
   hipLaunchKernelGGL((sk_reduce_kernel<T, NC, NP, APOL, R>), grid, dim3(SK_THREADS), 0, s, W, C, MN, G, GW);
 }
 
+// Blocks of 256 chains (one for each component of B when both operands are MC) up to which
+// the chains' latency is what counts, and sk_chain_kernel the faster one; on larger grids
+// sk_kernel's higher occupancy keeps more loads in flight.  Matrix-vector products, us
+// with sk_kernel -> sk_chain_kernel:
+//   MC x MC    f32 nc 2: 500 blocks 19.3 -> 11.5, 512 15.8 -> 14.3, 1000 20.9 -> 23.1; nc 3:
+//              750 40.8 -> 37.6, 768 36.8 -> 32.7, 1500 40.0 -> 72.5; f64 nc 2: 512 19.9 -> 16.6,
+//              1000 25.3 -> 36.3; f16 nc 2: 500 21.4 -> 16.4, 4096 74.9 -> 64.1
+//   MC, plain  f32 nc 3: 125 blocks 21.7 -> 13.5, 250 22.0 -> 15.6, 256 16.0 -> 19.6; f64 nc 2: 250
+//              15.6 -> 13.6; f16 nc 2: 250 13.3 -> 15.6, nc 3: 500 26.5 -> 24.2
+//   plain, MC  f32 nc 3: 250 blocks 17.4 -> 12.5, 500 17.6 -> 14.2, 2048 42.8 -> 48.6; f64 nc 2: 500
+//              18.5 -> 16.8
+// nc = 1 (two operations a step) gains nothing; binary32 nc = 4 with one MC operand loses
+// (22.7 -> 33.1 us at 62 slices of 64 steps): the components beyond what a binary64 value
+// fills are zero or nearly, and its short slices start with many general steps.
+static bool sk_chain_wanted(int size, int nc, bool a_mc, bool b_mc, int64_t blocks) {
+  if (nc == 1 || (size == 4 && nc == 4 && !(a_mc && b_mc))) return false;
+  if (size == 2) return a_mc && b_mc ? blocks <= 4096 : (nc >= 3 && blocks <= 512);
+  return blocks <= (a_mc && b_mc ? 768 : (a_mc ? 255 : 512));
+}
+
 template <typename T, int NC, bool AMC, bool BMC>
 static hipError_t sk_launch(int64_t M, int64_t N, int64_t K, const void *A, const void *B, int64_t S, void *W, void *C,
                             hipStream_t s) {
@@ -315,8 +442,14 @@ static hipError_t sk_launch(int64_t M, int64_t N, int64_t K, const void *A, cons
   // S <= SPLITK_MAX_SLICES = 2^20 gives G <= 4096 = 16 x 256 group roots.
   if (G > 16 * SK_THREADS) return hipErrorInvalidValue;
   dim3 grid((unsigned)((MN + (SK_THREADS / KS) - 1) / (SK_THREADS / KS)), (unsigned)G);
-  hipLaunchKernelGGL((sk_kernel<T, NC, AMC, BMC, SPOL, APOL>), grid, dim3(SK_THREADS), 0, s, (const T *)A,
-                     (const T *)B, (T *)C, (T *)W, M, N, K, S, KS, G);
+  if (sk_chain_wanted(sizeof(T), NC, AMC, BMC, (int64_t)grid.x * G * NP)) {
+    constexpr int ROLE = AMC ? SEQ_AMC : SEQ_BMC;
+    hipLaunchKernelGGL((sk_chain_kernel<T, NC, ROLE>), grid, dim3(SK_THREADS * NP), SK_THREADS * NP * NC * sizeof(T), s,
+                       (const T *)A, (const T *)B, (T *)C, (T *)W, M, N, K, S, KS, G, NP, (const T *)nullptr, N);
+  } else {
+    hipLaunchKernelGGL((sk_kernel<T, NC, AMC, BMC, SPOL, APOL>), grid, dim3(SK_THREADS), 0, s, (const T *)A,
+                       (const T *)B, (T *)C, (T *)W, M, N, K, S, KS, G);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || G == 1) return e;
   // W: the G group roots.
@@ -347,6 +480,40 @@ static hipError_t sk_dispatch(int nc, int64_t M, int64_t N, int64_t K, const voi
     case 4: return sk_kinds<T, 4>(M, N, K, A, a_mc, B, b_mc, S, W, C, s);
   }
   return hipErrorInvalidValue;
+}
+
+// The sums of one linear-regression step in one launch: C = r^T [X | r^(0) | r^(1) | ...],
+// [nc][d + nc], the K-split products of the MC residual r [nc][n] with the columns of X
+// [n][d] and with its own components, S <= 256 slices (one group: no workspace).
+template <typename T, int NC>
+static hipError_t lr_sums(int64_t n, int64_t d, const void *X, const void *R, int64_t S, void *C, hipStream_t s) {
+  int KS, G;
+  splitk_shape(S, &KS, &G);
+  if (G != 1) return hipErrorInvalidValue;
+  const unsigned per = SK_THREADS / KS, blocks = (unsigned)((d + NC + per - 1) / per);
+  hipLaunchKernelGGL((sk_chain_kernel<T, NC, SEQ_AMC>), dim3(blocks), dim3(SK_THREADS), SK_THREADS * NC * sizeof(T), s,
+                     (const T *)R, (const T *)X, (T *)C, (T *)nullptr, (int64_t)1, d + NC, n, S, KS, G, 1, (const T *)R,
+                     d);
+  return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t lr_sums_nc(int nc, int64_t n, int64_t d, const void *X, const void *R, int64_t S, void *C,
+                             hipStream_t s) {
+  switch (nc) {
+    case 1: return lr_sums<T, 1>(n, d, X, R, S, C, s);
+    case 2: return lr_sums<T, 2>(n, d, X, R, S, C, s);
+    case 3: return lr_sums<T, 3>(n, d, X, R, S, C, s);
+    case 4: return lr_sums<T, 4>(n, d, X, R, S, C, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_linreg_sums(int dtype, int nc, int64_t n, int64_t d, const void *X, const void *R, int64_t S, void *C,
+                              hipStream_t s) {
+  if (dtype == 0) return lr_sums_nc<_Float16>(nc, n, d, X, R, S, C, s);
+  if (dtype == 2) return lr_sums_nc<double>(nc, n, d, X, R, S, C, s);
+  return lr_sums_nc<float>(nc, n, d, X, R, S, C, s);
 }
 
 hipError_t launch_matmul_splitk(int dtype, int nc, int64_t M, int64_t N, int64_t K, const void *A, int a_mc,

@@ -90,3 +90,21 @@ def test_linreg_graph_replay(mcf, dt, nc):
         assert_bits(to_host(lg), want[r][1], f"loss after replay {r}")
         mcf.mc_add(other, other, nc=nc)  # eager work between replays
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("dt", [np.float16, np.float32, np.float64])
+@pytest.mark.parametrize("nc", [1, 2, 4])
+@pytest.mark.parametrize("shape", [(300, 16), (300, 17), (16640, 2), (64, 5)])
+def test_linreg_paths(mcf, orc, dt, nc, shape):
+    """One step on either side of the residual kernel's feature limit and of one slice group
+    (one launch for every sum, or a K-split product each)."""
+    n, d = shape
+    X, y_neg, W, _ = inputs.linreg_inputs(n, d, nc, dt, seed=5)
+    slices = [mcf.mc_matmul_splitk_slices(1, k, n) for k in (d, 1)]
+    want_W, want_loss = orc.linreg_gd_step(X, y_neg, W, 0.05, slices_g=slices[0], slices_l=slices[1])
+    import torch
+
+    tW, loss = to_dev(W), torch.empty(nc, dtype=to_dev(W).dtype, device="cuda")
+    mcf.mc_linreg_gd_step(to_dev(X), to_dev(y_neg), tW, 0.05, loss=loss)
+    assert_bits(to_host(tW), want_W, f"W {dt.__name__} nc={nc} {shape}")
+    assert_bits(to_host(loss), want_loss, f"loss {dt.__name__} nc={nc} {shape}")

@@ -174,3 +174,27 @@ def test_bench_shapes(mcf, orc):
     cols = np.zeros_like(rows)
     want = orc.matmul_splitk(A, B[:1], nc=3, b_mc=False, slices=S, rows=rows, cols=cols)
     assert_bits(got[:, rows, cols], want, "mv 8192")
+
+
+@pytest.mark.parametrize("dt", [np.float16, np.float32, np.float64])
+@pytest.mark.parametrize("nc", [2, 3, 4])
+@pytest.mark.parametrize("kinds", [(True, True), (True, False), (False, True)])
+def test_chain_kernel(mcf, orc, dt, nc, kinds):
+    """Few blocks (sk_chain_kernel): slices shorter and longer than its groups of steps, one
+    and several slice groups, columns, and operands with zero components, values, rows and
+    columns."""
+    g = np.random.default_rng(760 + nc)
+    for M, N, K, S in ((1, 1, 1, 1), (3, 1, 37, 5), (1, 3, 200, 13), (5, 2, 1000, 64), (2, 1, 3001, 300), (40, 1, 700, 11)):
+        for holes in (False, True):
+            A = inputs.expansion(g, (M, K), nc if kinds[0] else 1, dt, 0.3)
+            B = inputs.expansion(g, (K, N), nc if kinds[1] else 1, dt, 0.3)
+            if holes:
+                for x in (A, B):
+                    pick = g.random(x.shape[1:])
+                    x[:, pick < 0.3] = 0
+                    x[-1][pick > 0.7] = 0
+                    x[0][pick > 0.97] = 0
+                A[:, M // 2, : K // 2] = 0
+            got = to_host(mcf.mc_matmul_splitk(to_dev(A), to_dev(B), nc=nc, a_mc=kinds[0], b_mc=kinds[1], slices=S))
+            want = orc.matmul_splitk(A, B, nc=nc, slices=S, a_mc=kinds[0], b_mc=kinds[1])
+            assert_bits(got, want, f"{dt.__name__} nc={nc} {kinds} {M}x{N}x{K} S={S} holes={holes}")
