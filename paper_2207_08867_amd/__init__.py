@@ -15,6 +15,7 @@ Tensor conventions (component-major):
 from __future__ import annotations
 
 import ctypes
+import math
 import os
 
 __all__ = [
@@ -97,7 +98,7 @@ def lib() -> ctypes.CDLL:
 
 
 def mc_status_str(status: int) -> str:
-    return lib().mc_status_str(int(status)).decode()
+    return (_lib or lib()).mc_status_str(int(status)).decode()
 
 
 def _check(status: int, what: str):
@@ -108,10 +109,25 @@ def _check(status: int, what: str):
         raise MCFError(msg)
 
 
-def _torch():
-    import torch
+# A small call is host-bound: its kernels take 2 to 4 us, so what the binding does per call
+# is most of its time.  The helpers below keep that short: torch is looked up once, device
+# pointers and the stream are plain integers (the library's argument types convert them),
+# and the current stream's handle is read without building a Stream object (a 7850-element
+# MC-SGD update, two calls: 21 -> 15 us).
+_DTYPE_CODES = {}
+_torch_module = None
+_raw_stream = None
 
-    return torch
+
+def _torch():
+    global _torch_module, _raw_stream
+    if _torch_module is None:
+        import torch
+
+        _DTYPE_CODES.update({torch.float16: MCF_F16, torch.float32: MCF_F32, torch.float64: MCF_F64})
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _torch_module = torch
+    return _torch_module
 
 
 def _code(t, scaled: bool) -> int:
@@ -125,40 +141,46 @@ def _code(t, scaled: bool) -> int:
 
 
 def _dtype_code(t) -> int:
-    torch = _torch()
-    if t.dtype == torch.float16:
-        return MCF_F16
-    if t.dtype == torch.float32:
-        return MCF_F32
-    if t.dtype == torch.float64:
-        return MCF_F64
-    raise TypeError(f"component dtype must be float16, float32 or float64, got {t.dtype}")
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        _torch()
+        code = _DTYPE_CODES.get(t.dtype)
+        if code is None:
+            raise TypeError(f"component dtype must be float16, float32 or float64, got {t.dtype}")
+    return code
 
 
-def _dev(t, name):
+def _dev(t, name) -> int:
     if not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(t) -> ctypes.c_void_p:
+def _stream(t) -> int:
+    """Handle of the current stream of t's device."""
     torch = _torch()
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    if _raw_stream is not None:
+        return _raw_stream(t.get_device())
+    return torch.cuda.current_stream(t.device).cuda_stream
+
+
+def _same(x, y) -> bool:
+    return x.dtype == y.dtype and x.get_device() == y.get_device()
 
 
 def _logical_shape(t, nc, is_mc, name):
+    shape = t.shape
     if is_mc:
-        if t.dim() < 1 or t.shape[0] != nc:
-            raise ValueError(f"{name}: MC operand must have shape (nc={nc}, ...), got {tuple(t.shape)}")
-        return tuple(t.shape[1:])
-    return tuple(t.shape)
+        if not shape or shape[0] != nc:
+            raise ValueError(f"{name}: MC operand must have shape (nc={nc}, ...), got {tuple(shape)}")
+        return shape[1:]
+    return shape
 
 
 def _binary(fn_name, x, y, nc, x_mc, y_mc, out, scaled=False):
-    torch = _torch()
-    if x.dtype != y.dtype or x.device != y.device:
+    if not _same(x, y):
         raise ValueError("operands must share dtype and device")
     sx = _logical_shape(x, nc, x_mc, "x")
     sy = _logical_shape(y, nc, y_mc, "y")
@@ -169,15 +191,13 @@ def _binary(fn_name, x, y, nc, x_mc, y_mc, out, scaled=False):
         sy = sy[1:]
     if sx != sy:
         raise ValueError(f"shape mismatch: {sx} vs {sy}")
-    n = 1
-    for d in sx:
-        n *= d
+    n = math.prod(sx)
     if out is None:
-        out = torch.empty((nc,) + sx, dtype=x.dtype, device=x.device)
-    elif out.shape != (nc,) + sx or out.dtype != x.dtype:
+        out = x.new_empty((nc, *sx))
+    elif out.shape != (nc, *sx) or out.dtype != x.dtype:
         raise ValueError("out has the wrong shape or dtype")
-    st = getattr(lib(), fn_name)(_code(x, scaled), nc, n, _dev(x, "x"), int(bool(x_mc)), _dev(y, "y"),
-                                 int(bool(y_mc)), _dev(out, "out"), _stream(x))
+    st = getattr(_lib or lib(), fn_name)(_code(x, scaled), nc, n, _dev(x, "x"), int(bool(x_mc)), _dev(y, "y"),
+                                         int(bool(y_mc)), _dev(out, "out"), _stream(x))
     _check(st, fn_name)
     return out
 
@@ -209,7 +229,7 @@ def mc_mul_slow(x, y, *, nc: int, out=None):
         out = torch.empty_like(x)
     elif out.shape != x.shape or out.dtype != x.dtype:
         raise ValueError("out has the wrong shape or dtype")
-    st = lib().mc_mul_slow(_dtype_code(x), nc, n, _dev(x, "x"), _dev(y, "y"), _dev(out, "out"), _stream(x))
+    st = (_lib or lib()).mc_mul_slow(_dtype_code(x), nc, n, _dev(x, "x"), _dev(y, "y"), _dev(out, "out"), _stream(x))
     _check(st, "mc_mul_slow")
     return out
 
@@ -223,7 +243,7 @@ def mc_square(x, *, nc: int, out=None):
         out = torch.empty_like(x)
     elif out.shape != x.shape or out.dtype != x.dtype:
         raise ValueError("out has the wrong shape or dtype")
-    _check(lib().mc_square(_dtype_code(x), nc, n, _dev(x, "x"), _dev(out, "out"), _stream(x)), "mc_square")
+    _check((_lib or lib()).mc_square(_dtype_code(x), nc, n, _dev(x, "x"), _dev(out, "out"), _stream(x)), "mc_square")
     return out
 
 
@@ -237,7 +257,7 @@ def mc_exp(x, *, nc: int, out=None):
     elif out.shape != x.shape or out.dtype != x.dtype:
         raise ValueError("out has the wrong shape or dtype")
     del s
-    _check(lib().mc_exp(_dtype_code(x), nc, n, _dev(x, "x"), _dev(out, "out"), _stream(x)), "mc_exp")
+    _check((_lib or lib()).mc_exp(_dtype_code(x), nc, n, _dev(x, "x"), _dev(out, "out"), _stream(x)), "mc_exp")
     return out
 
 
@@ -251,25 +271,25 @@ def mc_renorm(x, *, nc_out: int | None = None, mode: int = 0, out=None):
         out = torch.empty((nc_out,) + tuple(x.shape[1:]), dtype=x.dtype, device=x.device)
     elif out.shape != (nc_out,) + tuple(x.shape[1:]) or out.dtype != x.dtype:
         raise ValueError("out has the wrong shape or dtype")
-    st = lib().mc_renorm(_dtype_code(x), nc_in, nc_out, n, _dev(x, "x"), _dev(out, "out"), int(mode), _stream(x))
+    st = (_lib or lib()).mc_renorm(_dtype_code(x), nc_in, nc_out, n, _dev(x, "x"), _dev(out, "out"), int(mode),
+                                   _stream(x))
     _check(st, "mc_renorm")
     return out
 
 
 def _mm_operands(A, B, nc, a_mc, b_mc, out):
-    torch = _torch()
-    if A.dtype != B.dtype or A.device != B.device:
+    if not _same(A, B):
         raise ValueError("operands must share dtype and device")
     A3 = A if A.dim() == 3 else A.reshape((1,) + tuple(A.shape))
     B3 = B if B.dim() == 3 else B.reshape((1,) + tuple(B.shape))
-    if A3.shape[0] != (nc if a_mc else 1) or B3.shape[0] != (nc if b_mc else 1):
+    planes_a, M, K = A3.shape
+    planes_b, K2, N = B3.shape
+    if planes_a != (nc if a_mc else 1) or planes_b != (nc if b_mc else 1):
         raise ValueError("operand plane count does not match nc / kind")
-    M, K = A3.shape[1:]
-    K2, N = B3.shape[1:]
     if K != K2:
         raise ValueError(f"inner dimensions differ: {K} vs {K2}")
     if out is None:
-        out = torch.empty((nc, M, N), dtype=A.dtype, device=A.device)
+        out = A.new_empty((nc, M, N))
     elif out.shape != (nc, M, N) or out.dtype != A.dtype:
         raise ValueError("out has the wrong shape or dtype")
     return A3, B3, M, N, K, out
@@ -279,7 +299,7 @@ def mc_matmul(A, B, *, nc: int, a_mc: bool = True, b_mc: bool = True, out=None, 
     """C = A B in MM-MCN order.  A: (nc|1, M, K), B: (nc|1, K, N) -> (nc, M, N).
     scaled=True: float16 components with scaled low components."""
     A3, B3, M, N, K, out = _mm_operands(A, B, nc, a_mc, b_mc, out)
-    st = lib().mc_matmul(_code(A, scaled), nc, M, N, K, _dev(A3, "A"), int(bool(a_mc)), _dev(B3, "B"),
+    st = (_lib or lib()).mc_matmul(_code(A, scaled), nc, M, N, K, _dev(A3, "A"), int(bool(a_mc)), _dev(B3, "B"),
                          int(bool(b_mc)), _dev(out, "out"), _stream(A))
     _check(st, "mc_matmul")
     return out
@@ -291,7 +311,7 @@ def mc_matmul_pruned(A, B, *, nc: int, out=None):
     parts combined by Add-MCN.  Same error bound as mc_matmul, about half the work at
     nc = 3; not mc_matmul's bits.  A: (nc, M, K), B: (nc, K, N) -> (nc, M, N)."""
     A3, B3, M, N, K, out = _mm_operands(A, B, nc, True, True, out)
-    st = lib().mc_matmul_pruned(_dtype_code(A), nc, M, N, K, _dev(A3, "A"), _dev(B3, "B"), _dev(out, "out"),
+    st = (_lib or lib()).mc_matmul_pruned(_dtype_code(A), nc, M, N, K, _dev(A3, "A"), _dev(B3, "B"), _dev(out, "out"),
                                 _stream(A))
     _check(st, "mc_matmul_pruned")
     return out
@@ -299,7 +319,7 @@ def mc_matmul_pruned(A, B, *, nc: int, out=None):
 
 def mc_matmul_splitk_slices(M: int, N: int, K: int) -> int:
     """Default slice count of the K-split product for this shape."""
-    s = lib().mc_matmul_splitk_slices(M, N, K)
+    s = (_lib or lib()).mc_matmul_splitk_slices(M, N, K)
     _check(int(s) if s < 0 else 0, "mc_matmul_splitk_slices")
     return int(s)
 
@@ -307,7 +327,7 @@ def mc_matmul_splitk_slices(M: int, N: int, K: int) -> int:
 def mc_matmul_splitk_workspace(dtype_code: int, nc: int, M: int, N: int, K: int, a_mc: bool, b_mc: bool,
                                slices: int) -> int:
     """Workspace bytes the K-split product needs."""
-    w = lib().mc_matmul_splitk_workspace(dtype_code, nc, M, N, K, int(bool(a_mc)), int(bool(b_mc)), slices)
+    w = (_lib or lib()).mc_matmul_splitk_workspace(dtype_code, nc, M, N, K, int(bool(a_mc)), int(bool(b_mc)), slices)
     _check(int(w) if w < 0 else 0, "mc_matmul_splitk_workspace")
     return int(w)
 
@@ -326,8 +346,8 @@ def mc_matmul_splitk(A, B, *, nc: int, a_mc: bool = True, b_mc: bool = True, sli
         workspace = torch.empty(wb, dtype=torch.uint8, device=A.device)
     wp = _dev(workspace, "workspace") if workspace is not None else None
     wn = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    st = lib().mc_matmul_splitk(code, nc, M, N, K, _dev(A3, "A"), int(bool(a_mc)), _dev(B3, "B"), int(bool(b_mc)),
-                                int(slices), wp, wn, _dev(out, "out"), _stream(A))
+    st = (_lib or lib()).mc_matmul_splitk(code, nc, M, N, K, _dev(A3, "A"), int(bool(a_mc)), _dev(B3, "B"),
+                                          int(bool(b_mc)), int(slices), wp, wn, _dev(out, "out"), _stream(A))
     _check(st, "mc_matmul_splitk")
     return out
 
@@ -337,15 +357,16 @@ def mc_matmul_splitk_noalloc(A, B, *, nc: int, a_mc: bool = True, b_mc: bool = T
     (8 MiB) holds the partial tree roots, so nothing is allocated when `out` is
     given.  Raises ValueError (MCF_E_SCRATCH) when the call needs more scratch."""
     A3, B3, M, N, K, out = _mm_operands(A, B, nc, a_mc, b_mc, out)
-    st = lib().mc_matmul_splitk_noalloc(_dtype_code(A), nc, M, N, K, _dev(A3, "A"), int(bool(a_mc)), _dev(B3, "B"),
-                                        int(bool(b_mc)), int(slices), _dev(out, "out"), _stream(A))
+    st = (_lib or lib()).mc_matmul_splitk_noalloc(_dtype_code(A), nc, M, N, K, _dev(A3, "A"), int(bool(a_mc)),
+                                                  _dev(B3, "B"),
+                                                  int(bool(b_mc)), int(slices), _dev(out, "out"), _stream(A))
     _check(st, "mc_matmul_splitk_noalloc")
     return out
 
 
 def mc_matmul_exact_workspace(nc: int, M: int, N: int, K: int) -> int:
     """Workspace bytes the exact binary16 product needs."""
-    w = lib().mc_matmul_exact_workspace(MCF_F16, nc, M, N, K)
+    w = (_lib or lib()).mc_matmul_exact_workspace(MCF_F16, nc, M, N, K)
     _check(int(w) if w < 0 else 0, "mc_matmul_exact_workspace")
     return int(w)
 
@@ -367,7 +388,7 @@ def mc_matmul_exact(A, B, *, nc: int, a_mc: bool = True, b_mc: bool = True, b_tr
     if workspace is None:
         workspace = torch.empty(max(wb, 1), dtype=torch.uint8, device=A.device)
     wn = workspace.numel() * workspace.element_size()
-    st = lib().mc_matmul_exact(_dtype_code(A), nc, M, N, K, _dev(A3, "A"), int(bool(a_mc)), _dev(B3, "B"),
+    st = (_lib or lib()).mc_matmul_exact(_dtype_code(A), nc, M, N, K, _dev(A3, "A"), int(bool(a_mc)), _dev(B3, "B"),
                                int(bool(b_mc)), int(bool(b_trans)), _dev(workspace, "workspace"), wn,
                                _dev(out, "out"), _stream(A))
     _check(st, "mc_matmul_exact")
@@ -376,7 +397,7 @@ def mc_matmul_exact(A, B, *, nc: int, a_mc: bool = True, b_mc: bool = True, b_tr
 
 def mc_linreg_workspace(dtype_code: int, nc: int, n: int, d: int) -> int:
     """Workspace bytes of one linear-regression gradient-descent step."""
-    w = lib().mc_linreg_workspace(dtype_code, nc, n, d)
+    w = (_lib or lib()).mc_linreg_workspace(dtype_code, nc, n, d)
     _check(int(w) if w < 0 else 0, "mc_linreg_workspace")
     return int(w)
 
@@ -398,7 +419,7 @@ def mc_linreg_gd_step(X, y_neg, W, lr: float, *, loss=None, workspace=None):
     code = _dtype_code(W)
     if workspace is None:
         workspace = torch.empty(mc_linreg_workspace(code, nc, n, d), dtype=torch.uint8, device=W.device)
-    st = lib().mc_linreg_gd_step(code, nc, n, d, _dev(X, "X"), _dev(y_neg, "y_neg"), _dev(W, "W"), float(lr),
+    st = (_lib or lib()).mc_linreg_gd_step(code, nc, n, d, _dev(X, "X"), _dev(y_neg, "y_neg"), _dev(W, "W"), float(lr),
                                  _dev(workspace, "workspace"), workspace.numel() * workspace.element_size(),
                                  None if loss is None else _dev(loss, "loss"), _stream(W))
     _check(st, "mc_linreg_gd_step")
@@ -418,12 +439,12 @@ def mc_linear_fwd_exact(x, W, b=None, *, out=None, workspace=None):
         raise ValueError("dtype or bias shape mismatch")
     T = x.shape[0]
     if out is None:
-        out = torch.empty((nc, T, O), dtype=W.dtype, device=W.device)
+        out = W.new_empty((nc, T, O))
     elif tuple(out.shape) != (nc, T, O) or out.dtype != W.dtype:
         raise ValueError("out has the wrong shape or dtype")
     if workspace is None:
         workspace = torch.empty(max(mc_matmul_exact_workspace(nc, T, O, I), 1), dtype=torch.uint8, device=W.device)
-    st = lib().mc_linear_fwd_exact(_dtype_code(W), nc, T, I, O, _dev(x, "x"), _dev(W, "W"),
+    st = (_lib or lib()).mc_linear_fwd_exact(_dtype_code(W), nc, T, I, O, _dev(x, "x"), _dev(W, "W"),
                                    None if b is None else _dev(b, "b"), _dev(workspace, "workspace"),
                                    workspace.numel() * workspace.element_size(), _dev(out, "out"), _stream(W))
     _check(st, "mc_linear_fwd_exact")
@@ -442,18 +463,18 @@ def mc_linear_fwd(x, W, b=None, *, out=None, scaled: bool = False):
         raise ValueError("dtype or bias shape mismatch")
     T = x.shape[0]
     if out is None:
-        out = torch.empty((nc, T, O), dtype=W.dtype, device=W.device)
+        out = W.new_empty((nc, T, O))
     elif out.shape != (nc, T, O) or out.dtype != W.dtype:
         raise ValueError("out has the wrong shape or dtype")
     bp = _dev(b, "b") if b is not None else None
-    st = lib().mc_linear_fwd(_code(W, scaled), nc, T, I, O, _dev(x, "x"), _dev(W, "W"), bp, _dev(out, "out"),
+    st = (_lib or lib()).mc_linear_fwd(_code(W, scaled), nc, T, I, O, _dev(x, "x"), _dev(W, "W"), bp, _dev(out, "out"),
                              _stream(W))
     _check(st, "mc_linear_fwd")
     return out
 
 
 def mc_linear_bwd_workspace(dtype_code: int, nc: int, batch: int, in_: int, out: int) -> int:
-    w = lib().mc_linear_bwd_workspace(dtype_code, nc, batch, in_, out)
+    w = (_lib or lib()).mc_linear_bwd_workspace(dtype_code, nc, batch, in_, out)
     _check(int(w) if w < 0 else 0, "mc_linear_bwd_workspace")
     return int(w)
 
@@ -474,16 +495,15 @@ def mc_linear_bwd(x, W, dY, *, dy_mc: bool = True, dx: bool = True, dw: bool = T
     if x.dtype != W.dtype or dY.dtype != W.dtype:
         raise ValueError("dtype mismatch")
     code = _dtype_code(W)
-    outs = [torch.empty((nc, T, I), dtype=W.dtype, device=W.device) if dx else None,
-            torch.empty((nc, O, I), dtype=W.dtype, device=W.device) if dw else None,
-            torch.empty((nc, O), dtype=W.dtype, device=W.device) if db else None]
+    outs = [W.new_empty((nc, T, I)) if dx else None, W.new_empty((nc, O, I)) if dw else None,
+            W.new_empty((nc, O)) if db else None]
     if (dw or db) and workspace is None:
         workspace = torch.empty(max(mc_linear_bwd_workspace(code, nc, T, I, O), 1), dtype=torch.uint8,
                                 device=W.device)
     wp = _dev(workspace, "workspace") if workspace is not None else None
     wn = workspace.numel() * workspace.element_size() if workspace is not None else 0
     ptr = [(_dev(o, "out") if o is not None else None) for o in outs]
-    st = lib().mc_linear_bwd(code, nc, T, I, O, _dev(x, "x"), _dev(W, "W"), _dev(dY, "dY"), int(bool(dy_mc)),
+    st = (_lib or lib()).mc_linear_bwd(code, nc, T, I, O, _dev(x, "x"), _dev(W, "W"), _dev(dY, "dY"), int(bool(dy_mc)),
                              ptr[0], ptr[1], ptr[2], wp, wn, _stream(W))
     _check(st, "mc_linear_bwd")
     return tuple(outs)
@@ -528,8 +548,9 @@ def mc_matmul_batched(A, B, *, nc: int, a_mc: bool = True, b_mc: bool = True, ou
         raise ValueError("out has the wrong shape or dtype")
     ap, as1, as2 = _batch_strides(A, "A", b2, M, K)
     bp, bs1, bs2 = _batch_strides(B, "B", b2, K, N)
-    st = lib().mc_matmul_batched(_dtype_code(A), nc, b2[0], b2[1], M, N, K, _dev(A, "A"), int(bool(a_mc)), ap, as1,
-                                 as2, _dev(B, "B"), int(bool(b_mc)), bp, bs1, bs2, _dev(out, "out"), _stream(A))
+    st = (_lib or lib()).mc_matmul_batched(_dtype_code(A), nc, b2[0], b2[1], M, N, K, _dev(A, "A"), int(bool(a_mc)),
+                                           ap, as1,
+                                           as2, _dev(B, "B"), int(bool(b_mc)), bp, bs1, bs2, _dev(out, "out"), _stream(A))
     _check(st, "mc_matmul_batched")
     return out
 
@@ -556,7 +577,7 @@ def mc_addmm(A, B, Y, *, nc: int, alpha: float = 1.0, beta: float = 1.0, a_mc: b
         y_rows = 1
     else:
         raise ValueError(f"Y must be (nc, M, N) or (nc, N), got {tuple(Y.shape)}")
-    st = lib().mc_addmm(_dtype_code(A), nc, M, N, K, _dev(A3, "A"), int(bool(a_mc)), _dev(B3, "B"),
+    st = (_lib or lib()).mc_addmm(_dtype_code(A), nc, M, N, K, _dev(A3, "A"), int(bool(a_mc)), _dev(B3, "B"),
                         int(bool(b_mc)), _dev(Y, "Y"), y_rows, float(alpha), float(beta), _dev(out, "out"),
                         _stream(A))
     _check(st, "mc_addmm")
