@@ -30,7 +30,8 @@
 // v_mfma_i32_16x16x64_i8.  Block (s, kb, rb) of an operand with RB row blocks and KB
 // k blocks starts at ((s * KB + kb) * RB + rb) KiB.
 //
-// Kernels: xs_init clears the level statistics and the non-finite flags; xs_slice
+// Kernels: xs_init clears the level statistics and the non-finite flags (large operands
+// only, see XBLOCK_WORDS); xs_slice
 // writes the digit planes of both operands (four bytes of every level per lane, so
 // that stores are contiguous) and records, per operand, the lowest and highest
 // digit level in use; xm_kernel runs the contraction over the levels in use, with one
@@ -69,6 +70,17 @@ constexpr int XSLOTS = 64;
 constexpr int XBADW = 4 * XSLOTS * 64;
 constexpr int XSTAT_WORDS = XBADW + 64;
 
+// Operands of at most XBLOCK_WORDS blocks (16 rows x 64 k) in all: every slicing workgroup
+// stores one word of its own instead -- its highest level + 1 (bits 0-7), XD - its lowest
+// (8-15) and the rows with a non-finite component (16-31) -- and the readers reduce them
+// all, so nothing has to be cleared first by a launch of its own.  Word kb RB + rb of an
+// operand, B's words after A's, in the place of the slots.  MC-Linear nc = 3, us a call with
+// slots -> words: 16 x 64 x 64 18.7 -> 16.3, 64 x 512 x 512 28.9 -> 26.1, 1000 x 1024 x 1024 (2048
+// blocks) 46.0 -> 44.2; but 4096 x 1024 x 1024 (5120 blocks, read by 1024 workgroups) 95.9
+// -> 103.0.
+constexpr int64_t XBLOCK_WORDS = 2560;
+static_assert(XBLOCK_WORDS <= XSTAT_WORDS, "");
+
 // binary16 bits -> the exact integer value * 2^24 (finite inputs)
 __device__ __forceinline__ int64_t f16_units(uint32_t b) {
   const uint32_t e = (b >> 10) & 31u, m = b & 1023u;
@@ -88,6 +100,7 @@ struct SliceOp {
   int8_t *D;             // XD planes of Rp x Kp digits in fragment order
   uint8_t *bad;          // per-row non-finite flags
   uint32_t *stats;       // the statistics block
+  uint32_t *words;       // this operand's block words, or null: the slots
   int64_t chunks;        // 16-byte chunks per level: Rp * Kp / 16
 };
 
@@ -95,8 +108,11 @@ struct SliceOp {
 // one atomic maximum per kind into the workgroup's slot (no value returned, so the
 // workgroup does not wait for it; the XSLOTS slots keep same-address atomics few).
 // Every lane of the workgroup must call this.
-__device__ __forceinline__ void x_stats(uint32_t *stats, int kind_hi, int kind_lo, uint32_t top, uint32_t low) {
-  __shared__ uint32_t red[2][XS_THREADS / 64];
+// With block words: one store of block blk's word; bad: the lane's row, (lane / 4) % 16, has
+// a non-finite component.
+__device__ __forceinline__ void x_stats(uint32_t *stats, int kind_hi, int kind_lo, uint32_t top, uint32_t low,
+                                        uint32_t *words, int64_t blk, bool bad) {
+  __shared__ uint32_t red[3][XS_THREADS / 64];
   const uint32_t wtop = __ockl_wfred_max_u32(top);
   const uint32_t wlow = __ockl_wfred_max_u32(XD - low);
   const int wave = threadIdx.x / 64;
@@ -104,12 +120,27 @@ __device__ __forceinline__ void x_stats(uint32_t *stats, int kind_hi, int kind_l
     red[0][wave] = wtop;
     red[1][wave] = wlow;
   }
+  if (words != nullptr) {  // uniform
+    const uint64_t bad_lanes = __builtin_amdgcn_ballot_w64(bad);
+    if (threadIdx.x % 64 == 0) {
+      uint32_t rows = 0;
+      if (bad_lanes != 0)
+        for (int r = 0; r < 16; ++r) rows |= (uint32_t)(((bad_lanes >> (4 * r)) & 15) != 0) << r;
+      red[2][wave] = rows;
+    }
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
     uint32_t bt = 0, bl = 0;
     for (int w = 0; w < XS_THREADS / 64; ++w) {
       bt = max(bt, red[0][w]);
       bl = max(bl, red[1][w]);
+    }
+    if (words != nullptr) {
+      uint32_t rows = 0;
+      for (int w = 0; w < XS_THREADS / 64; ++w) rows |= red[2][w];
+      words[blk] = bt | bl << 8 | rows << 16;
+      return;
     }
     const int slot = (int)(blockIdx.x % XSLOTS) * 64;
     uint32_t *hi = stats + (kind_hi * XSLOTS) * 64 + slot, *lo = stats + (kind_lo * XSLOTS) * 64 + slot;
@@ -175,6 +206,7 @@ __global__ __launch_bounds__(XS_THREADS) void xs_slice(SliceOp a, SliceOp b, int
   const SliceOp &o = is_a ? a : b;
   const int64_t t = (int64_t)(is_a ? blockIdx.x : blockIdx.x - a_blocks) * XS_THREADS + threadIdx.x;
   uint32_t top = 0, low = XD;
+  bool bad = false;
   if (t < 4 * o.chunks) {
     const int64_t u = t / 4;
     const int part = (int)(t % 4);
@@ -185,7 +217,6 @@ __global__ __launch_bounds__(XS_THREADS) void xs_slice(SliceOp a, SliceOp b, int
     const int64_t row = rb * 16 + l % 16;
     const int64_t k0 = kb * 64 + 16 * (l / 16) + 4 * part;
     int64_t X[4] = {0, 0, 0, 0};
-    bool bad = false;
     if (row < o.R) {
       // Every load of the lane is issued before any is used, so the lane waits for
       // memory once rather than once per plane (the plane count is uniform per
@@ -197,7 +228,7 @@ __global__ __launch_bounds__(XS_THREADS) void xs_slice(SliceOp a, SliceOp b, int
         case 3: slice_entries<3>(o, p, k0, K, X, bad); break;
         default: slice_entries<4>(o, p, k0, K, X, bad); break;
       }
-      if (bad) {
+      if (bad && o.words == nullptr) {
         o.bad[row] = 1;
         o.stats[XBADW] = 1;
       }
@@ -228,7 +259,9 @@ __global__ __launch_bounds__(XS_THREADS) void xs_slice(SliceOp a, SliceOp b, int
     }
   }
   // every lane of the workgroup takes part in the reductions
-  x_stats(o.stats, is_a ? 0 : 1, is_a ? 2 : 3, top, low);
+  static_assert(XS_THREADS == 4 * 64, "a workgroup slices one block");
+  x_stats(o.stats, is_a ? 0 : 1, is_a ? 2 : 3, top, low, o.words,
+          (int64_t)(is_a ? blockIdx.x : blockIdx.x - a_blocks), bad);
 }
 
 // ---------------------------------------------------------------------------------
@@ -297,6 +330,7 @@ struct XmArgs {
   const int8_t *DA, *DB;
   const uint8_t *bad_a, *bad_b;
   const uint32_t *stats;
+  const uint32_t *words;  // block words (A's, then B's), or null: the slots and row flags
   int64_t M, N, Kp, Mp, Np;
   int nc;
   uint16_t *C;       // [nc][M][N]
@@ -312,20 +346,47 @@ struct XLevels {
   bool anybad;  // some input component is infinite or NaN
 };
 
-// The first wavefront reads slot l of each kind in lane l and reduces; the result
-// reaches the other wavefronts through LDS.  Every lane of the workgroup must call
-// this (it holds a barrier).
-__device__ __forceinline__ XLevels x_levels(const uint32_t *stats) {
+// Slots: the first wavefront reads slot l of each kind in lane l and reduces.  Block
+// words: the workgroup reads them all.  The result reaches every wavefront through LDS.
+// Every lane of the workgroup must call this (it holds barriers).
+template <bool WORDS>
+__device__ __forceinline__ XLevels x_levels(const XmArgs &g) {
   __shared__ uint32_t sw[5];
+  __shared__ uint32_t part[5][8];
   XLevels v;
-  if (threadIdx.x < 64) {
+  if constexpr (WORDS) {
+    const int na = (int)(g.Kp / 64 * (g.Mp / 16)), n = na + (int)(g.Kp / 64 * (g.Np / 16));
+    uint32_t m[5] = {0, 0, 0, 0, 0};
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+      const uint32_t w = g.words[i];
+      const uint32_t hi = w & 0xFFu, lo = (w >> 8) & 0xFFu;
+      const bool a = i < na;
+      m[0] = max(m[0], a ? hi : 0u);
+      m[1] = max(m[1], a ? 0u : hi);
+      m[2] = max(m[2], a ? lo : 0u);
+      m[3] = max(m[3], a ? 0u : lo);
+      m[4] |= w >> 16;
+    }
+    const int wave = threadIdx.x / 64, waves = blockDim.x / 64;
+#pragma unroll
+    for (int kind = 0; kind < 5; ++kind) {
+      const uint32_t r = __ockl_wfred_max_u32(m[kind]);
+      if (threadIdx.x % 64 == 0) part[kind][wave] = r;
+    }
+    __syncthreads();
+    if (threadIdx.x < 5) {
+      uint32_t r = 0;
+      for (int w = 0; w < waves; ++w) r = max(r, part[threadIdx.x][w]);
+      sw[threadIdx.x] = r;
+    }
+  } else if (threadIdx.x < 64) {
     const int l = threadIdx.x;
 #pragma unroll
     for (int kind = 0; kind < 4; ++kind) {
-      const uint32_t m = __ockl_wfred_max_u32(stats[(kind * XSLOTS + l) * 64]);
+      const uint32_t m = __ockl_wfred_max_u32(g.stats[(kind * XSLOTS + l) * 64]);
       if (l == 0) sw[kind] = m;
     }
-    if (l == 0) sw[4] = stats[XBADW];
+    if (l == 0) sw[4] = g.stats[XBADW];
   }
   __syncthreads();
   v.anybad = sw[4] != 0;
@@ -339,6 +400,31 @@ __device__ __forceinline__ XLevels x_levels(const uint32_t *stats) {
   v.nB = hiB > v.loB ? hiB - v.loB : 0;
   v.small = v.nA <= 3 && v.nB <= 3;
   return v;
+}
+
+// Block words: rows 16 blk .. 16 blk + 15 of an operand (A, or B's rows: columns of the
+// product) with a non-finite component, as bits.
+__device__ __forceinline__ uint32_t x_bad_rows(const XmArgs &g, bool is_a, int64_t blk) {
+  const int64_t KB = g.Kp / 64, RA = g.Mp / 16, RB = g.Np / 16;
+  const uint32_t *w = is_a ? g.words : g.words + KB * RA;
+  uint32_t m = 0;
+  for (int64_t kb = 0; kb < KB; ++kb) m |= w[kb * (is_a ? RA : RB) + blk] >> 16;
+  return m;
+}
+
+// The bad rows of the workgroup's 64 x 64 tile: words 0-3 A's row blocks, 4-7 B's.  Set by
+// xm_kernel when some component is not finite.
+__device__ __forceinline__ uint32_t *x_tile_bad() {
+  __shared__ uint32_t rows[8];
+  return rows;
+}
+
+template <bool WORDS>
+__device__ __forceinline__ bool x_bad(const XmArgs &g, const XLevels &lv, int64_t row, int64_t col) {
+  if constexpr (!WORDS) return g.bad_a[row] | g.bad_b[col];
+  if (!lv.anybad) return false;
+  const uint32_t *t = x_tile_bad();
+  return ((t[(row & 63) >> 4] >> (row & 15)) | (t[4 + ((col & 63) >> 4)] >> (col & 15))) & 1;
 }
 
 // The bias of column col as an exact integer in units of 2^-24 (0 without a bias);
@@ -389,7 +475,7 @@ __device__ __forceinline__ uint32_t take_f16_binary64(double &d) {
 // i of lane l is row 4 (l / 16) + i, column l % 16 of its tile, one int32 accumulator
 // per tile and shift class).  stage: 16-byte aligned LDS of at least 2560 bytes owned by
 // this wavefront.
-template <int DM, int WTR, int WTC>
+template <int DM, int WTR, int WTC, bool WORDS>
 __device__ __forceinline__ void xm_epilogue(const XmArgs &g, const XLevels &lv, v4i (&acc)[2 * DM - 1][WTR][WTC],
                                             int64_t row0, int64_t col0, int64_t chunk, int64_t S, uint16_t *st) {
   constexpr int NCLS = 2 * DM - 1;
@@ -546,7 +632,7 @@ __device__ __forceinline__ void xm_epilogue(const XmArgs &g, const XLevels &lv, 
           } else {
             bool bb = false;
             const int64_t b = bias_units(g, col, bb);
-            store_split(V + (i128)((u128)(i128)b << 24), g.nc, g.bad_a[row] | g.bad_b[col] | bb, g.C, MN, idx);
+            store_split(V + (i128)((u128)(i128)b << 24), g.nc, x_bad<WORDS>(g, lv, row, col) | bb, g.C, MN, idx);
           }
         }
       }
@@ -562,7 +648,7 @@ __device__ __forceinline__ void xm_epilogue(const XmArgs &g, const XLevels &lv, 
 // exchange accumulators through LDS (red: 16 KiB, exact integer sums) so that each
 // holds the complete sums of one tile row, and each rounds its row.  Every lane of the
 // workgroup must call it then (it holds barriers).
-template <int DM, int WTR, int WTC, int KS = 1>
+template <int DM, int WTR, int WTC, bool WORDS, int KS = 1>
 __device__ __forceinline__ void xm_tile(const XmArgs &g, const XLevels &lv, int64_t row0, int64_t col0,
                                         int64_t chunk, int64_t kb0, int64_t kb1, int64_t S, uint16_t *st,
                                         int khalf = 0, int *red = nullptr) {
@@ -664,10 +750,10 @@ __device__ __forceinline__ void xm_tile(const XmArgs &g, const XLevels &lv, int6
         for (int i = 0; i < 4; ++i) mine[q][0][c][i] += red[((qw * 2 + (1 - khalf)) * 8 + c * 4 + i) * 64 + lane];
       __syncthreads();
     }
-    xm_epilogue<DM, 1, WTC>(g, lv, mine, row0 + 16 * khalf, col0, chunk, S, st);
+    xm_epilogue<DM, 1, WTC, WORDS>(g, lv, mine, row0 + 16 * khalf, col0, chunk, S, st);
     return;
   }
-  xm_epilogue<DM, WTR, WTC>(g, lv, acc, row0, col0, chunk, S, st);
+  xm_epilogue<DM, WTR, WTC, WORDS>(g, lv, acc, row0, col0, chunk, S, st);
 }
 
 // One workgroup of 4 KS wavefronts per 64 x 64 tile of C; blockIdx.y is the K chunk.
@@ -678,17 +764,22 @@ __device__ __forceinline__ void xm_tile(const XmArgs &g, const XLevels &lv, int6
 // Otherwise: four passes over the 32 x 32 quarters, each wavefront taking one 16 x 16
 // tile (eleven classes).  The second group of wavefronts of a KS = 2 workgroup takes
 // part in the three-level path only.
-template <int KS>
+template <int KS, bool WORDS>
 __global__ __attribute__((amdgpu_flat_work_group_size(1, 256 * KS), amdgpu_waves_per_eu(2))) void xm_kernel(
     XmArgs g) {
   // epilogue staging: 2560 bytes per wavefront; KS = 2 exchange: 16 KiB of the same
   // memory, used before the epilogue
   __shared__ __attribute__((aligned(16))) int8_t smem[KS == 2 ? 8 * 2560 : 4 * 2560];
-  const XLevels lv = x_levels(g.stats);
+  const XLevels lv = x_levels<WORDS>(g);
   const int wave = (threadIdx.x / 64) % 4;
   const int khalf = threadIdx.x / 256;
   const int64_t tile = blockIdx.x;
   const int64_t tm = tile / g.tiles_n, tn = tile - tm * g.tiles_n;
+  if (WORDS && lv.anybad) {  // uniform
+    if (threadIdx.x < 8)
+      x_tile_bad()[threadIdx.x] = x_bad_rows(g, threadIdx.x < 4, (threadIdx.x < 4 ? tm : tn) * 4 + threadIdx.x % 4);
+    __syncthreads();
+  }
   const int64_t KB = g.Kp / 64;
   const int64_t chunk = blockIdx.y;
   const int dm = lv.small ? 3 : (lv.nA <= 4 && lv.nB <= 4 ? 4 : 6);
@@ -699,23 +790,24 @@ __global__ __attribute__((amdgpu_flat_work_group_size(1, 256 * KS), amdgpu_waves
   const int64_t S = KB == 0 ? 1 : (KB + CKB - 1) / CKB;
   uint16_t *st = (uint16_t *)(smem + (threadIdx.x / 64) * 2560);
   if (dm == 3) {
-    xm_tile<3, 2, 2, KS>(g, lv, tm * 64 + (wave / 2) * 32, tn * 64 + (wave % 2) * 32, chunk, kb0, kb1, S, st, khalf,
+    xm_tile<3, 2, 2, WORDS, KS>(g, lv, tm * 64 + (wave / 2) * 32, tn * 64 + (wave % 2) * 32, chunk, kb0, kb1, S, st, khalf,
                          (int *)smem);
     return;
   }
   if (khalf) return;
   if (dm == 4) {
     for (int sub = 0; sub < 2; ++sub)
-      xm_tile<4, 2, 1>(g, lv, tm * 64 + (wave / 2) * 32, tn * 64 + sub * 32 + (wave % 2) * 16, chunk, kb0, kb1, S, st);
+      xm_tile<4, 2, 1, WORDS>(g, lv, tm * 64 + (wave / 2) * 32, tn * 64 + sub * 32 + (wave % 2) * 16, chunk, kb0, kb1, S, st);
   } else {
     for (int sub = 0; sub < 4; ++sub)
-      xm_tile<6, 1, 1>(g, lv, tm * 64 + (sub / 2) * 32 + (wave / 2) * 16, tn * 64 + (sub % 2) * 32 + (wave % 2) * 16,
+      xm_tile<6, 1, 1, WORDS>(g, lv, tm * 64 + (sub / 2) * 32 + (wave / 2) * 16, tn * 64 + (sub % 2) * 32 + (wave % 2) * 16,
                        chunk, kb0, kb1, S, st);
   }
 }
 
+template <bool WORDS>
 __global__ void xm_finish(XmArgs g) {
-  const XLevels lv = x_levels(g.stats);  // every lane, before any returns
+  const XLevels lv = x_levels<WORDS>(g);  // every lane, before any returns
   const int dm = lv.small ? 3 : (lv.nA <= 4 && lv.nB <= 4 ? 4 : 6);
   const int64_t chunk_kb = x_chunk(dm) / 64;
   const int64_t KB = g.Kp / 64;
@@ -729,7 +821,13 @@ __global__ void xm_finish(XmArgs g) {
   const int64_t row = t / g.N, col = t - row * g.N;
   bool bb = false;
   const int64_t b = bias_units(g, col, bb);
-  store_split(V + (i128)((u128)(i128)b << 24), g.nc, g.bad_a[row] | g.bad_b[col] | bb, g.C, MN, t);
+  bool bad;
+  if constexpr (WORDS)
+    bad = lv.anybad && ((x_bad_rows(g, true, row / 16) >> (row % 16) |
+                         x_bad_rows(g, false, col / 16) >> (col % 16)) & 1);
+  else
+    bad = g.bad_a[row] | g.bad_b[col];
+  store_split(V + (i128)((u128)(i128)b << 24), g.nc, bad | bb, g.C, MN, t);
 }
 
 int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
@@ -774,7 +872,9 @@ hipError_t launch_matmul_exact(int nc, int64_t M, int64_t N, int64_t K, const vo
   uint8_t *bad_a = (uint8_t *)(w + L.off_bad_a), *bad_b = (uint8_t *)(w + L.off_bad_b);
   int8_t *DA = (int8_t *)(w + L.off_da), *DB = (int8_t *)(w + L.off_db);
 
-  {
+  const int64_t a_words = L.Kp / XKSTEP * (L.Mp / 16), b_words = L.Kp / XKSTEP * (L.Np / 16);
+  uint32_t *words = a_words + b_words <= XBLOCK_WORDS ? stats : nullptr;
+  if (words == nullptr) {
     const int64_t n = M > N ? M : N;
     const int64_t nb = (n > 4 * XSLOTS ? n : 4 * XSLOTS);
     const int blocks = (int)((nb + 255) / 256 < 1024 ? (nb + 255) / 256 : 1024);
@@ -794,6 +894,7 @@ hipError_t launch_matmul_exact(int nc, int64_t M, int64_t N, int64_t K, const vo
     a.D = DA;
     a.bad = bad_a;
     a.stats = stats;
+    a.words = words;
     a.chunks = L.Mp * L.Kp / 16;
     b.src = (const uint16_t *)B;
     b.planes = b_mc ? nc : 1;
@@ -807,6 +908,7 @@ hipError_t launch_matmul_exact(int nc, int64_t M, int64_t N, int64_t K, const vo
     b.D = DB;
     b.bad = bad_b;
     b.stats = stats;
+    b.words = words != nullptr ? words + a_words : nullptr;
     b.chunks = L.Np * L.Kp / 16;
     const int64_t ab = (4 * a.chunks + XS_THREADS - 1) / XS_THREADS;
     const int64_t bb = (4 * b.chunks + XS_THREADS - 1) / XS_THREADS;
@@ -818,6 +920,7 @@ hipError_t launch_matmul_exact(int nc, int64_t M, int64_t N, int64_t K, const vo
   g.bad_a = bad_a;
   g.bad_b = bad_b;
   g.stats = stats;
+  g.words = words;
   g.M = M;
   g.N = N;
   g.Kp = L.Kp;
@@ -834,13 +937,15 @@ hipError_t launch_matmul_exact(int nc, int64_t M, int64_t N, int64_t K, const vo
     // fewer workgroups than two per compute unit: split each tile's k blocks over two
     // wavefronts per quarter
     if (tiles * L.Smax < 512)
-      hipLaunchKernelGGL(xm_kernel<2>, dim3((unsigned)tiles, (unsigned)L.Smax), dim3(512), 0, stream, g);
+      hipLaunchKernelGGL((words ? xm_kernel<2, true> : xm_kernel<2, false>), dim3((unsigned)tiles, (unsigned)L.Smax),
+                         dim3(512), 0, stream, g);
     else
-      hipLaunchKernelGGL(xm_kernel<1>, dim3((unsigned)tiles, (unsigned)L.Smax), dim3(256), 0, stream, g);
+      hipLaunchKernelGGL((words ? xm_kernel<1, true> : xm_kernel<1, false>), dim3((unsigned)tiles, (unsigned)L.Smax),
+                         dim3(256), 0, stream, g);
   }
   if (L.Smax > 1) {
     const int64_t n = M * N;
-    hipLaunchKernelGGL(xm_finish, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, g);
+    hipLaunchKernelGGL((words ? xm_finish<true> : xm_finish<false>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, g);
   }
   return hipGetLastError();
 }

@@ -216,3 +216,27 @@ def test_exact_linear_layer_with_bias_sampled(mcf):
     WT = np.ascontiguousarray(np.swapaxes(W, 1, 2))
     assert_bits(got[:, r, c], xp.matmul_exact(X[None], WT, nc=nc, a_mc=False, bias=b, rows=r, cols=c),
                 "linear 4096x1024x1024 with bias")
+
+
+@pytest.mark.parametrize("shape", [(70, 130, 200), (3, 5, 10000), (3, 5, 20000), (3, 5, 34000), (700, 40, 4000)])
+def test_exact_nonfinite_block_words(mcf, shape):
+    """Level statistics and non-finite rows kept per block (at most 2560 blocks of 16 rows x 64
+    k) and in slots, with and without partial sums: entries in the first and last row,
+    column and block, then the same call with finite operands in the same workspace."""
+    import torch
+
+    M, N, K = shape
+    nc = 2
+    A, B = operands(M, N, K, nc, 2700)
+    A[0, 1] *= np.float16(64)  # more levels than three
+    ws = torch.full((mcf.mc_matmul_exact_workspace(nc, M, N, K),), 255, dtype=torch.uint8, device="cuda")
+    bad_A, bad_B = A.copy(), B.copy()
+    bad_A[1, M - 1, K - 1] = np.inf
+    bad_A[0, 0, 3] = np.nan
+    bad_B[0, K - 1, N - 1] = -np.inf
+    g = np.random.default_rng(2701)
+    r, c = g.integers(0, M, 60), g.integers(0, N, 60)
+    r[:20], c[10:30] = np.where(np.arange(20) % 2, M - 1, 0), np.where(np.arange(20) % 3, N - 1, 0)
+    for X, Y, what in ((bad_A, bad_B, "non-finite"), (A, B, "finite after it")):
+        got = to_host(mcf.mc_matmul_exact(to_dev(X), to_dev(Y), nc=nc, workspace=ws))
+        assert_bits(got[:, r, c], xp.matmul_exact(X, Y, nc=nc, rows=r, cols=c), f"{what} {shape}")
