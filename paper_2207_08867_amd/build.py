@@ -32,7 +32,12 @@ CFLAGS = [
     "-fno-gpu-flush-denormals-to-zero", "-fno-slp-vectorize",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
+    # an unroll request that the compiler drops fails the build: the product kernels lose
+    # 3% when their reduction loops are not unrolled
+    "-Werror=pass-failed",
 ]
+# Files with loops that stay rolled: a wavefront vote in the body (Exp-MCN).
+ROLLED = ("elementwise.hip", "exp64.hip")
 
 
 def build(verbose: bool = False) -> str:
@@ -46,6 +51,8 @@ def build(verbose: bool = False) -> str:
         cmd = [HIPCC, *CFLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
         if src.endswith(".cpp"):
             cmd[1:1] = ["-x", "hip"]
+        if src in ROLLED:
+            cmd.append("-Wno-pass-failed")
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
@@ -54,7 +61,7 @@ def build(verbose: bool = False) -> str:
         out, _ = p.communicate()
         if p.returncode != 0:
             failed.append((src, out))
-        elif verbose and out.strip():
+        elif "warning:" in out or (verbose and out.strip()):
             print(out, flush=True)
     if failed:
         for src, out in failed:

@@ -347,18 +347,7 @@ struct Lane {
   template <int PMASK, bool TPS, bool ORD, int DEPTH = 1>
   __device__ __forceinline__ void run(const T (*As)[KT][BM], const T (*Bs)[KT][BN], int kk0, int kt, int tx,
                                       int ty) {
-    // two steps per loop iteration, so the accumulators keep their registers across
-    // the back edge instead of being copied
-    if constexpr (PRUNE) {
-#pragma unroll 2
-      for (int kk = kk0; kk < kt; ++kk) {
-        Ops o;
-        o.load(As, Bs, kk, tx, ty);
-        prune_step<0, PMASK, TPS, false>(o);
-      }
-      return;
-    }
-    if constexpr (SPOL == SR_SUFFIX && NC == 2) {
+    if constexpr (!PRUNE && SPOL == SR_SUFFIX && NC == 2) {
       // nc = 2: the tests of two steps share one branch.  (For nc >= 3 grouping keeps
       // more temporaries live, lowers the wavefronts per SIMD and was measured
       // slower; there each step tests and branches on its own, below.)
@@ -379,7 +368,7 @@ struct Lane {
       if (kk < kt) group_kept<PMASK, TPS, 1, ORD>(As, Bs, kk, tx, ty);
       return;
     }
-    if constexpr (DEPTH > 1 && !GROUP) {
+    if constexpr (!PRUNE && DEPTH > 1 && !GROUP) {
       // The operands of DEPTH steps are read from LDS first, then the steps run on them
       // in k order: for binary32 grids of few wavefronts, where nothing hides a step's
       // LDS latency, and for the binary16 MC-Linear kernel.
@@ -406,19 +395,32 @@ struct Lane {
       }
       return;
     }
-#pragma unroll 2
-    for (int kk = kk0; kk < kt; ++kk) {
-      Ops o;
-      o.load(As, Bs, kk, tx, ty);
-      if constexpr (SPOL == SR_SUFFIX) {
-        kept_step<PMASK, TPS, ORD>(o);
-      } else if constexpr (GROUP) {
-        T term[NP][TM][TN][NC];
-        scale<PMASK>(o, term);
-        add<PMASK>(term);
-      } else {
-        full_step<PMASK>(o);
-      }
+    // Two steps per loop iteration, so the accumulators keep their registers across the
+    // back edge instead of being copied.  Written out: prod_err's asm counts as convergent,
+    // and a convergent loop is not unrolled where that leaves a remainder.
+    int kk = kk0;
+    for (; kk + 1 < kt; kk += 2) {
+      step<PMASK, TPS, ORD>(As, Bs, kk, tx, ty);
+      step<PMASK, TPS, ORD>(As, Bs, kk + 1, tx, ty);
+    }
+    if (kk < kt) step<PMASK, TPS, ORD>(As, Bs, kk, tx, ty);
+  }
+
+  // Reduction step kk.
+  template <int PMASK, bool TPS, bool ORD>
+  __device__ __forceinline__ void step(const T (*As)[KT][BM], const T (*Bs)[KT][BN], int kk, int tx, int ty) {
+    Ops o;
+    o.load(As, Bs, kk, tx, ty);
+    if constexpr (PRUNE) {
+      prune_step<0, PMASK, TPS, false>(o);
+    } else if constexpr (SPOL == SR_SUFFIX) {
+      kept_step<PMASK, TPS, ORD>(o);
+    } else if constexpr (GROUP) {
+      T term[NP][TM][TN][NC];
+      scale<PMASK>(o, term);
+      add<PMASK>(term);
+    } else {
+      full_step<PMASK>(o);
     }
   }
 
