@@ -396,14 +396,20 @@ struct Lane {
       return;
     }
     // Two steps per loop iteration, so the accumulators keep their registers across the
-    // back edge instead of being copied.  Written out: prod_err's asm counts as convergent,
-    // and a convergent loop is not unrolled where that leaves a remainder.
-    int kk = kk0;
-    for (; kk + 1 < kt; kk += 2) {
-      step<PMASK, TPS, ORD>(As, Bs, kk, tx, ty);
-      step<PMASK, TPS, ORD>(As, Bs, kk + 1, tx, ty);
+    // back edge instead of being copied.  binary16: written out, since prod_err's asm counts
+    // as convergent and a convergent loop is not unrolled where that leaves a remainder.
+    // (The pruned binary32 product is 5% slower written out: 256^3 nc = 3 85 -> 89 us.)
+    if constexpr (sizeof(T) == 2) {
+      int kk = kk0;
+      for (; kk + 1 < kt; kk += 2) {
+        step<PMASK, TPS, ORD>(As, Bs, kk, tx, ty);
+        step<PMASK, TPS, ORD>(As, Bs, kk + 1, tx, ty);
+      }
+      if (kk < kt) step<PMASK, TPS, ORD>(As, Bs, kk, tx, ty);
+    } else {
+#pragma unroll 2
+      for (int kk = kk0; kk < kt; ++kk) step<PMASK, TPS, ORD>(As, Bs, kk, tx, ty);
     }
-    if (kk < kt) step<PMASK, TPS, ORD>(As, Bs, kk, tx, ty);
   }
 
   // Reduction step kk.
