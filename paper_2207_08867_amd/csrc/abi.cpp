@@ -25,8 +25,10 @@ bool bad_alias(const void *out, int64_t obytes, const void *in, int64_t ibytes) 
   return overlap(out, obytes, in, ibytes);
 }
 
-// The sequential product launches one workgroup per 16 x 16 (or larger) tile of C in
-// a 1-D grid, which must stay below 2^31 workgroups.
+// The sequential product numbers its tiles of C, 256 outputs or more each, with 31 bits.
+// One launch holds fewer than 2^32 lanes: results of one component take as many launches
+// as they need; with more components the runtime refuses the launch (MCF_E_HIP) from 2^32
+// outputs on (2^33 where a lane has two outputs).
 bool grid_fits(int64_t M, int64_t N) { return ((M + 15) / 16) * ((N + 15) / 16) < ((int64_t)1 << 31); }
 
 // a * b elements stay below 2^50, so byte counts (times nc and the element size) and

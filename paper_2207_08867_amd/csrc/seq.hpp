@@ -49,6 +49,7 @@ struct SeqArgs {
   int64_t B2, bb0, a_s1, a_s2, b_s1, b_s2;
   int np;     // planes of the plain side, each a product of its own (MC x MC: nc), else 1
   int tx_log; // TX = 1 << tx_log columns by 256 / TX rows per workgroup
+  uint32_t tile0;  // the launch's first tile
   int vec_a, vec_b;  // 16-byte loads are aligned and never cross an edge
   int mode;   // epilogue, as MmArgs
   T alpha, beta;
@@ -277,7 +278,8 @@ seq_kernel(const SeqArgs<T> g) {
   const int lane = threadIdx.x & (SEQ_LANES - 1), p = threadIdx.x / SEQ_LANES;
   const int tx = lane & (BN - 1), ty = lane >> tx_log;
   const uint32_t gx = (uint32_t)((g.N + BN - 1) >> tx_log);
-  const int64_t m0 = (int64_t)(blockIdx.x / gx) << ty_log, n0 = (int64_t)(blockIdx.x % gx) << tx_log;
+  const uint32_t tile = g.tile0 + blockIdx.x;
+  const int64_t m0 = (int64_t)(tile / gx) << ty_log, n0 = (int64_t)(tile % gx) << tx_log;
   const T *A = g.A, *B = g.B;
   const int64_t bb = g.bb0 + blockIdx.y;
   if (bb != 0) {
@@ -455,13 +457,20 @@ hipError_t seq_launch(SeqArgs<T> g, int64_t batches, hipStream_t s) {
   int lds = 2 * rows * SEQ_STRIDE;
   const int parts = (g.np - 1) * NC * SEQ_LANES * (int)sizeof(T);
   if (parts > lds) lds = parts;
-  const unsigned tiles = (unsigned)(((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn));
-  for (int64_t b0 = 0; b0 < batches; b0 += 65535) {  // batches go to grid y
+  const int64_t tiles = ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
+  // batches go to grid y, tiles to grid x; a launch holds fewer than 2^32 lanes along x, so
+  // results of one component with 2^31 outputs or more take several
+  const int64_t most = ((int64_t)1 << 31) / (SEQ_LANES * g.np);
+  for (int64_t b0 = 0; b0 < batches; b0 += 65535) {
     g.bb0 = b0;
     const unsigned nb = (unsigned)(batches - b0 < 65535 ? batches - b0 : 65535);
-    hipLaunchKernelGGL((seq_kernel<T, NC, ROLE, AT, BT>), dim3(tiles, nb), dim3(SEQ_LANES * g.np), lds, s, g);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    for (int64_t t0 = 0; t0 < tiles; t0 += most) {
+      g.tile0 = (uint32_t)t0;
+      const unsigned nt = (unsigned)(tiles - t0 < most ? tiles - t0 : most);
+      hipLaunchKernelGGL((seq_kernel<T, NC, ROLE, AT, BT>), dim3(nt, nb), dim3(SEQ_LANES * g.np), lds, s, g);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
   }
   return hipSuccess;
 }

@@ -91,3 +91,18 @@ def test_ragged_above_the_limit(mcf, orc, dt, nc, kinds):
     rows[:40], cols[40:80] = M - 1, N - 1
     got = to_host(mcf.mc_matmul(to_dev(A), to_dev(B), nc=nc, a_mc=kinds[0], b_mc=kinds[1]))[:, rows, cols]
     assert_bits(got, orc.matmul(A, B, nc=nc, a_mc=kinds[0], b_mc=kinds[1], rows=rows, cols=cols), f"{dt} {nc} {kinds}")
+
+
+def test_one_component_beyond_one_launch(mcf):
+    """2^32 + 2^16 outputs of one component: more lanes than one launch holds along x.  K = 1,
+    so every output is the rounded product of two values."""
+    import torch
+
+    M, N = 65536, 65537
+    g = torch.Generator(device="cuda")
+    g.manual_seed(960)
+    a = (torch.rand(M, generator=g, device="cuda") + 0.5).half()
+    b = (torch.rand(N, generator=g, device="cuda") + 0.5).half()
+    out = mcf.mc_matmul(a[None, :, None], b[None, None, :], nc=1)[0]
+    for r in range(0, M, 4096):
+        assert torch.equal(out[r : r + 4096], a[r : r + 4096, None] * b[None, :]), r
