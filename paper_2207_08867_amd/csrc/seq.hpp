@@ -50,7 +50,6 @@ struct SeqArgs {
   int np;     // planes of the plain side, each a product of its own (MC x MC: nc), else 1
   int tx_log; // TX = 1 << tx_log columns by 256 / TX rows per workgroup
   uint32_t tile0;  // the launch's first tile
-  int vec_a, vec_b;  // 16-byte loads are aligned and never cross an edge
   int mode;   // epilogue, as MmArgs
   T alpha, beta;
   // When last is given, column N - 1 of B is not stored: it holds ones, and that column
@@ -203,12 +202,16 @@ __device__ __forceinline__ void seq_steps(const SeqOps<T, NC, ROLE, U> &o, T (&a
 }
 
 // One lane's piece of a plane's tile: 16 bytes along the contiguous dimension of an
-// operand stored [rows][K] (KC) or [K][rows].
+// operand stored [rows][K] (KC) or [K][rows].  One load wherever 16 bytes from its start
+// lie inside the matrix, whatever the alignment: the ISA allows it, and rows of ragged
+// sizes start anywhere (with a load per element instead, 711 x 1803 x 196 binary16 nc = 1
+// took 48 us, and K = 17 to 250 lost up to a fifth to mm_kernel's loads).
 template <typename T, bool KC>
 struct SeqPiece {
   static constexpr int VW = 16 / (int)sizeof(T);
   int row, k, rows;  // first tile row and step of the piece; rows of it inside the operand
   bool active;
+  bool spare;      // elements of the next stored row follow this one's, VW or more (!KC: if there is one)
   int64_t offset;  // of the piece from the operand's plane
   __device__ __forceinline__ SeqPiece(int lane, int rows_log, int64_t r0, int64_t limit, int64_t ld) {
     if constexpr (KC) {
@@ -222,27 +225,34 @@ struct SeqPiece {
     const int64_t left = limit - (r0 + row);
     const int most = KC ? 1 : VW;
     rows = !active || left <= 0 ? 0 : (left < most ? (int)left : most);
+    spare = ld >= VW && (!KC || left > 1);
     offset = KC ? (r0 + row) * ld + k : (int64_t)k * ld + r0 + row;
   }
-  // The piece at src, k_left steps before the end of the reduction, zeros outside the
-  // operand.  vec: a 16-byte load is aligned wherever it lies inside the operand.  one:
-  // the element that holds one instead (VW: none).
-  __device__ __forceinline__ seq_u32x4 load(const T *src, int64_t k_left, bool vec, int one) const {
+  // The piece at src, k_left steps before the end of the reduction: zeros for steps past
+  // it, any values for rows outside the operand (their outputs are not wanted).  one: the
+  // element that holds one instead (VW: none).
+  __device__ __forceinline__ seq_u32x4 load(const T *src, int64_t k_left, int one) const {
     const int64_t left = k_left - k;
     const int n = rows == 0 || left <= 0 ? 0 : (KC ? (left < VW ? (int)left : VW) : rows);
-    seq_u32x4 r = {0, 0, 0, 0};
-    if (vec && n == VW) {
-      r = *reinterpret_cast<const seq_u32x4 *>(src);
-    } else if (n > 0 || (!KC && one < VW)) {
-      T e[VW];
+    T e[VW];
+    if (n == VW || (n > 0 && spare && (KC || left > 1))) {
+      __builtin_memcpy(e, src, 16);
+      if (KC && n < VW) {
+#pragma unroll
+        for (int i = 0; i < VW; ++i) e[i] = i < n ? e[i] : T(0);
+      }
+    } else {
 #pragma unroll
       for (int i = 0; i < VW; ++i) e[i] = i < n ? src[i] : T(0);
-      if constexpr (!KC) {
-#pragma unroll
-        for (int i = 0; i < VW; ++i) e[i] = i == one && left > 0 ? T(1) : e[i];
-      }
-      __builtin_memcpy(&r, e, 16);
     }
+    if constexpr (!KC) {
+      if (one < VW && left > 0) {
+#pragma unroll
+        for (int i = 0; i < VW; ++i) e[i] = i == one ? T(1) : e[i];
+      }
+    }
+    seq_u32x4 r;
+    __builtin_memcpy(&r, e, 16);
     return r;
   }
   // to: the plane's tile in LDS
@@ -307,9 +317,9 @@ seq_kernel(const SeqArgs<T> g) {
   auto fetch = [&](int64_t k0) {
 #pragma unroll
     for (int c = 0; c < NA; ++c)
-      if (g.np == 1 || c % g.np == p) reg_a[c] = pa.load(src_a + c * g.a_plane, K - k0, g.vec_a, VW);
+      if (g.np == 1 || c % g.np == p) reg_a[c] = pa.load(src_a + c * g.a_plane, K - k0, VW);
 #pragma unroll
-    for (int c = 0; c < NBS; ++c) reg_b[c] = pb.load(src_b + c * g.b_plane, K - k0, g.vec_b, one);
+    for (int c = 0; c < NBS; ++c) reg_b[c] = pb.load(src_b + c * g.b_plane, K - k0, one);
     src_a += AT ? (int64_t)KT * g.a_ld : (int64_t)KT;
     src_b += BT ? (int64_t)KT : (int64_t)KT * g.b_ld;
   };
@@ -447,12 +457,8 @@ inline int seq_tx_log(int64_t M, int64_t N) {
 
 template <typename T, int NC, int ROLE, bool AT, bool BT>
 hipError_t seq_launch(SeqArgs<T> g, int64_t batches, hipStream_t s) {
-  constexpr int VW = 16 / (int)sizeof(T);
   g.tx_log = seq_tx_log(g.M, g.N);
   const int bn = 1 << g.tx_log, bm = SEQ_LANES / bn;
-  auto mult = [](int64_t v) { return v % VW == 0; };
-  g.vec_a = mult(g.a_ld) && mult(g.a_plane) && mult(g.a_s1) && mult(g.a_s2) && (uintptr_t)g.A % 16 == 0;
-  g.vec_b = mult(g.b_ld) && mult(g.b_plane) && mult(g.b_s1) && mult(g.b_s2) && (uintptr_t)g.B % 16 == 0;
   const int rows = (ROLE == SEQ_AMC ? NC : 1) * bm + (ROLE == SEQ_BMC ? NC : g.np) * bn;
   int lds = 2 * rows * SEQ_STRIDE;
   const int parts = (g.np - 1) * NC * SEQ_LANES * (int)sizeof(T);

@@ -106,3 +106,20 @@ def test_one_component_beyond_one_launch(mcf):
     out = mcf.mc_matmul(a[None, :, None], b[None, None, :], nc=1)[0]
     for r in range(0, M, 4096):
         assert torch.equal(out[r : r + 4096], a[r : r + 4096, None] * b[None, :]), r
+
+
+@pytest.mark.parametrize("dt", FORMATS)
+@pytest.mark.parametrize("kinds", KINDS)
+def test_neighbours_stay_out(mcf, orc, dt, kinds):
+    """A 16-byte piece that crosses the end of a row or column reads what is stored next: with
+    infinities and NaNs in every second row of A and column of B, the other outputs keep the
+    oracle's bits, at rows and columns of every remainder and of fewer elements than a piece."""
+    g = np.random.default_rng(970)
+    for M, N, K in ((6, 9, 33), (5, 46, 17), (3, 3, 3), (9, 2, 70), (4, 15, 1), (33, 23, 31)):
+        A = operand(g, (M, K), 2 if kinds[0] else 1, dt, False)
+        B = operand(g, (K, N), 2 if kinds[1] else 1, dt, False)
+        A[:, 1::2, :], B[:, :, 1::2] = np.inf, np.nan
+        got = to_host(mcf.mc_matmul(to_dev(A), to_dev(B), nc=2, a_mc=kinds[0], b_mc=kinds[1]))[:, ::2, ::2]
+        want = orc.matmul(np.ascontiguousarray(A[:, ::2]), np.ascontiguousarray(B[:, :, ::2]), nc=2, a_mc=kinds[0],
+                          b_mc=kinds[1])
+        assert_bits(np.ascontiguousarray(got), want, f"{dt.__name__} {kinds} {M}x{N}x{K}")
