@@ -160,10 +160,15 @@ __device__ __forceinline__ bool seq_group(const SeqOps<T, NC, ROLE, U> &o, T (&a
 // U steps into acc: the straight line, then the general algorithm for lanes that fail.
 // again(o2) reads the operands again (binary32 and binary64, for the strict test), from
 // somewhere the compiler cannot know, or it would keep the terms of the first attempt in
-// registers; one(u, x, v) reads those of step u.  strict: the wavefront's state; valid:
-// the lane's result is wanted; first: these are the first steps of the reduction.
+// registers; one(u, x, v) reads those of step u.  valid: the lane's result is wanted;
+// first: these are the first steps of the reduction.
+// fails: the wavefront's state, how many of its groups failed the first test.  After two it
+// stays with the strict test, since what fails again is a property of its data; one alone
+// is a term that came out zero by chance, and a wavefront that left the first test for it
+// would be the slowest of the grid (256^2 x 256 binary32 nc = 3, plain A: 43 us when the
+// first failure counted, 31 us now).
 template <typename T, int NC, int ROLE, int U, typename Again, typename One>
-__device__ __forceinline__ void seq_steps(const SeqOps<T, NC, ROLE, U> &o, T (&acc)[NC], bool &strict, bool valid,
+__device__ __forceinline__ void seq_steps(const SeqOps<T, NC, ROLE, U> &o, T (&acc)[NC], int &fails, bool valid,
                                           bool first, const Again &again, const One &one) {
   constexpr int NX = SeqOps<T, NC, ROLE, U>::NX;
   T saved[NC];
@@ -173,13 +178,12 @@ __device__ __forceinline__ void seq_steps(const SeqOps<T, NC, ROLE, U> &o, T (&a
   if constexpr (sizeof(T) == 2) {
     bad = seq_group<T, NC, ROLE, U, true>(o, acc);
   } else {
-    if (!strict) {
+    if (fails < 2) {
       bad = seq_group<T, NC, ROLE, U, false>(o, acc);
       if (__builtin_expect(NC == 1 || !__any(bad && valid), 1)) return;
-      // The wavefront stays with the other test, since what failed is a property of its
-      // data; not so the first steps of plain factors, whose accumulator has no third
-      // component yet.
-      strict = ROLE != SEQ_PLAIN || !first;
+      // (not counted: the first steps of plain factors, whose accumulator has no third
+      // component yet)
+      fails += ROLE != SEQ_PLAIN || !first;
 #pragma unroll
       for (int c = 0; c < NC; ++c) acc[c] = saved[c];
     }
@@ -350,7 +354,7 @@ seq_kernel(const SeqArgs<T> g) {
   }
   __syncthreads();
   int buf = 0;
-  bool strict = false;
+  int fails = 0;
   for (int64_t k0 = 0; k0 < K; k0 += KT, buf ^= 1) {
     const bool more = k0 + KT < K;
     if (more) fetch(k0 + KT);
@@ -365,7 +369,7 @@ seq_kernel(const SeqArgs<T> g) {
     };
     auto steps = [&](const Ops &o, int kk) {
       seq_steps<T, NC, ROLE, U>(
-          o, acc, strict, valid, k0 + kk == 0,
+          o, acc, fails, valid, k0 + kk == 0,
           [&](Ops &o2) {
             int at = kk;
             asm volatile("" : "+s"(at));

@@ -245,10 +245,10 @@ void sk_chain_kernel(const T *__restrict__ A, const T *__restrict__ B, T *__rest
         for (int c = 0; c < NC; ++c) ops.x[c][u] = x[c];
       }
     };
-    bool strict = false;
+    int fails = 0;
     auto steps = [&](const Ops &ops, int64_t k) {
       seq_steps<T, NC, ROLE, U>(
-          ops, acc, strict, true, k == s,
+          ops, acc, fails, true, k == s,
           [&](Ops &o2) {
             int64_t at = k;
             asm volatile("" : "+v"(at));

@@ -123,3 +123,22 @@ def test_neighbours_stay_out(mcf, orc, dt, kinds):
         want = orc.matmul(np.ascontiguousarray(A[:, ::2]), np.ascontiguousarray(B[:, :, ::2]), nc=2, a_mc=kinds[0],
                           b_mc=kinds[1])
         assert_bits(np.ascontiguousarray(got), want, f"{dt.__name__} {kinds} {M}x{N}x{K}")
+
+
+@pytest.mark.parametrize("dt", [np.float32, np.float64])
+@pytest.mark.parametrize("nc", [2, 3])
+@pytest.mark.parametrize("kinds", KINDS)
+@pytest.mark.parametrize("zeros", [1, 2, 5])
+def test_zero_terms_by_chance(mcf, orc, dt, nc, kinds, zeros):
+    """Dense operands with a zero term in one, two and five groups of steps of one row and one
+    column: wavefronts that go back to the first test after one, and stay with the other after two."""
+    M, N, K = 37, 41, 130
+    g = np.random.default_rng(980 + nc)
+    A = operand(g, (M, K), nc if kinds[0] else 1, dt, False)
+    B = operand(g, (K, N), nc if kinds[1] else 1, dt, False)
+    for i in range(zeros):
+        A[:, 5, 19 + 21 * i] = 0
+        B[:, 30 + 21 * i, 7] = 0
+    got = to_host(mcf.mc_matmul(to_dev(A), to_dev(B), nc=nc, a_mc=kinds[0], b_mc=kinds[1]))
+    want = orc.matmul(A, B, nc=nc, a_mc=kinds[0], b_mc=kinds[1])
+    assert_bits(got, want, f"{dt.__name__} nc={nc} {kinds} zeros={zeros}")
