@@ -50,6 +50,7 @@ struct SeqArgs {
   int np;     // planes of the plain side, each a product of its own (MC x MC: nc), else 1
   int tx_log; // TX = 1 << tx_log columns by 256 / TX rows per workgroup
   uint32_t tile0;  // the launch's first tile
+  int vec_a, vec_b;  // 16-byte loads are aligned and never cross an edge
   int mode;   // epilogue, as MmArgs
   T alpha, beta;
   // When last is given, column N - 1 of B is not stored: it holds ones, and that column
@@ -178,7 +179,8 @@ __device__ __forceinline__ void seq_steps(const SeqOps<T, NC, ROLE, U> &o, T (&a
   if constexpr (sizeof(T) == 2) {
     bad = seq_group<T, NC, ROLE, U, true>(o, acc);
   } else {
-    if (fails < 2) {
+    // (binary32 nc = 4: one failure, the fourth component that a binary64 value leaves empty)
+    if (fails < (sizeof(T) == 4 && NC == 4 ? 1 : 2)) {
       bad = seq_group<T, NC, ROLE, U, false>(o, acc);
       if (__builtin_expect(NC == 1 || !__any(bad && valid), 1)) return;
       // (not counted: the first steps of plain factors, whose accumulator has no third
@@ -206,16 +208,17 @@ __device__ __forceinline__ void seq_steps(const SeqOps<T, NC, ROLE, U> &o, T (&a
 }
 
 // One lane's piece of a plane's tile: 16 bytes along the contiguous dimension of an
-// operand stored [rows][K] (KC) or [K][rows].  One load wherever 16 bytes from its start
-// lie inside the matrix, whatever the alignment: the ISA allows it, and rows of ragged
-// sizes start anywhere (with a load per element instead, 711 x 1803 x 196 binary16 nc = 1
-// took 48 us, and K = 17 to 250 lost up to a fifth to mm_kernel's loads).
-template <typename T, bool KC>
+// operand stored [rows][K] (KC) or [K][rows].
+// ANY: rows of ragged sizes.  A piece is one 16-byte load wherever 16 bytes from its start lie
+// inside the matrix, at any alignment (the ISA allows it).  binary16 only: a load per element
+// costs it eight a piece (711 x 1803 x 196 nc = 1 48 us against 26), binary32 and binary64,
+// with four and two, gain nothing.
+template <typename T, bool KC, bool ANY>
 struct SeqPiece {
   static constexpr int VW = 16 / (int)sizeof(T);
   int row, k, rows;  // first tile row and step of the piece; rows of it inside the operand
   bool active;
-  bool spare;      // elements of the next stored row follow this one's, VW or more (!KC: if there is one)
+  bool spare;      // ANY: elements of the next stored row follow this one's, VW or more (!KC: if there is one)
   int64_t offset;  // of the piece from the operand's plane
   __device__ __forceinline__ SeqPiece(int lane, int rows_log, int64_t r0, int64_t limit, int64_t ld) {
     if constexpr (KC) {
@@ -232,31 +235,37 @@ struct SeqPiece {
     spare = ld >= VW && (!KC || left > 1);
     offset = KC ? (r0 + row) * ld + k : (int64_t)k * ld + r0 + row;
   }
-  // The piece at src, k_left steps before the end of the reduction: zeros for steps past
-  // it, any values for rows outside the operand (their outputs are not wanted).  one: the
-  // element that holds one instead (VW: none).
-  __device__ __forceinline__ seq_u32x4 load(const T *src, int64_t k_left, int one) const {
+  // The piece at src, k_left steps before the end of the reduction, zeros outside the
+  // operand (ANY: any values for rows outside it, whose outputs are not wanted).  vec: a
+  // 16-byte load is aligned wherever it lies inside the operand.  one: the element that
+  // holds one instead (VW: none).
+  __device__ __forceinline__ seq_u32x4 load(const T *src, int64_t k_left, bool vec, int one) const {
     const int64_t left = k_left - k;
     const int n = rows == 0 || left <= 0 ? 0 : (KC ? (left < VW ? (int)left : VW) : rows);
-    T e[VW];
-    if (n == VW || (n > 0 && spare && (KC || left > 1))) {
-      __builtin_memcpy(e, src, 16);
-      if (KC && n < VW) {
+    seq_u32x4 r = {0, 0, 0, 0};
+    if (ANY ? n == VW || (n > 0 && spare && (KC || left > 1)) : vec && n == VW) {
+      if constexpr (ANY) {
+        __builtin_memcpy(&r, src, 16);
+        if ((KC && n < VW) || (!KC && one < VW)) {
+          T e[VW];
+          __builtin_memcpy(e, &r, 16);
 #pragma unroll
-        for (int i = 0; i < VW; ++i) e[i] = i < n ? e[i] : T(0);
+          for (int i = 0; i < VW; ++i) e[i] = KC ? (i < n ? e[i] : T(0)) : (i == one ? T(1) : e[i]);
+          __builtin_memcpy(&r, e, 16);
+        }
+      } else {
+        r = *reinterpret_cast<const seq_u32x4 *>(src);
       }
-    } else {
+    } else if (n > 0 || (!KC && one < VW)) {
+      T e[VW];
 #pragma unroll
       for (int i = 0; i < VW; ++i) e[i] = i < n ? src[i] : T(0);
-    }
-    if constexpr (!KC) {
-      if (one < VW && left > 0) {
+      if constexpr (!KC) {
 #pragma unroll
-        for (int i = 0; i < VW; ++i) e[i] = i == one ? T(1) : e[i];
+        for (int i = 0; i < VW; ++i) e[i] = i == one && left > 0 ? T(1) : e[i];
       }
+      __builtin_memcpy(&r, e, 16);
     }
-    seq_u32x4 r;
-    __builtin_memcpy(&r, e, 16);
     return r;
   }
   // to: the plane's tile in LDS
@@ -276,7 +285,7 @@ struct SeqPiece {
 
 // AT: A is stored [K][M] (rows a_ld apart) instead of [M][K]; BT: B is stored [N][K]
 // instead of [K][N].
-template <typename T, int NC, int ROLE, bool AT, bool BT>
+template <typename T, int NC, int ROLE, bool AT, bool BT, bool ANY>
 __global__ __attribute__((amdgpu_flat_work_group_size(SEQ_LANES, ROLE == SEQ_AMC ? SEQ_LANES * NC : SEQ_LANES))) void
 seq_kernel(const SeqArgs<T> g) {
   constexpr int VW = 16 / (int)sizeof(T);
@@ -308,8 +317,8 @@ seq_kernel(const SeqArgs<T> g) {
   // contiguous dimension, one per lane of a 256-lane group; group p stages the planes of
   // A that are p modulo np, and plane p of B (every plane when np is 1).
   constexpr int NBS = ROLE == SEQ_BMC ? NC : 1;
-  const SeqPiece<T, !AT> pa(lane, ty_log, m0, g.M, g.a_ld);
-  const SeqPiece<T, BT> pb(lane, tx_log, n0, n_stored, g.b_ld);
+  const SeqPiece<T, !AT, ANY> pa(lane, ty_log, m0, g.M, g.a_ld);
+  const SeqPiece<T, BT, ANY> pb(lane, tx_log, n0, n_stored, g.b_ld);
   // column of ones: element `one` of this lane's piece of B
   const int one = !BT && g.last != nullptr && pb.active && n_stored >= n0 + pb.row && n_stored < n0 + pb.row + VW
                       ? (int)(n_stored - n0) - pb.row
@@ -321,9 +330,9 @@ seq_kernel(const SeqArgs<T> g) {
   auto fetch = [&](int64_t k0) {
 #pragma unroll
     for (int c = 0; c < NA; ++c)
-      if (g.np == 1 || c % g.np == p) reg_a[c] = pa.load(src_a + c * g.a_plane, K - k0, VW);
+      if (g.np == 1 || c % g.np == p) reg_a[c] = pa.load(src_a + c * g.a_plane, K - k0, g.vec_a, VW);
 #pragma unroll
-    for (int c = 0; c < NBS; ++c) reg_b[c] = pb.load(src_b + c * g.b_plane, K - k0, one);
+    for (int c = 0; c < NBS; ++c) reg_b[c] = pb.load(src_b + c * g.b_plane, K - k0, g.vec_b, one);
     src_a += AT ? (int64_t)KT * g.a_ld : (int64_t)KT;
     src_b += BT ? (int64_t)KT : (int64_t)KT * g.b_ld;
   };
@@ -461,8 +470,12 @@ inline int seq_tx_log(int64_t M, int64_t N) {
 
 template <typename T, int NC, int ROLE, bool AT, bool BT>
 hipError_t seq_launch(SeqArgs<T> g, int64_t batches, hipStream_t s) {
+  constexpr int VW = 16 / (int)sizeof(T);
   g.tx_log = seq_tx_log(g.M, g.N);
   const int bn = 1 << g.tx_log, bm = SEQ_LANES / bn;
+  auto mult = [](int64_t v) { return v % VW == 0; };
+  g.vec_a = mult(g.a_ld) && mult(g.a_plane) && mult(g.a_s1) && mult(g.a_s2) && (uintptr_t)g.A % 16 == 0;
+  g.vec_b = mult(g.b_ld) && mult(g.b_plane) && mult(g.b_s1) && mult(g.b_s2) && (uintptr_t)g.B % 16 == 0;
   const int rows = (ROLE == SEQ_AMC ? NC : 1) * bm + (ROLE == SEQ_BMC ? NC : g.np) * bn;
   int lds = 2 * rows * SEQ_STRIDE;
   const int parts = (g.np - 1) * NC * SEQ_LANES * (int)sizeof(T);
@@ -477,7 +490,11 @@ hipError_t seq_launch(SeqArgs<T> g, int64_t batches, hipStream_t s) {
     for (int64_t t0 = 0; t0 < tiles; t0 += most) {
       g.tile0 = (uint32_t)t0;
       const unsigned nt = (unsigned)(tiles - t0 < most ? tiles - t0 : most);
-      hipLaunchKernelGGL((seq_kernel<T, NC, ROLE, AT, BT>), dim3(nt, nb), dim3(SEQ_LANES * g.np), lds, s, g);
+      if (sizeof(T) == 2 && !(g.vec_a && g.vec_b))
+        hipLaunchKernelGGL((seq_kernel<T, NC, ROLE, AT, BT, sizeof(T) == 2>), dim3(nt, nb), dim3(SEQ_LANES * g.np), lds, s,
+                           g);
+      else
+        hipLaunchKernelGGL((seq_kernel<T, NC, ROLE, AT, BT, false>), dim3(nt, nb), dim3(SEQ_LANES * g.np), lds, s, g);
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
