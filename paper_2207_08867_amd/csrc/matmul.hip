@@ -934,35 +934,69 @@ static hipError_t mm_typed(const MmLaunch &L, hipStream_t s) {
 
 // Grids of few wavefronts take the kernel of seq.hpp, which overlaps the steps of one
 // output's chain but needs more registers (3 or 4 wavefronts per SIMD at nc = 3): up to
-// how many blocks of 256 outputs per CU it is the faster one, by format, kind and nc.
-// Measured at K = 256 (time of mm_kernel over seq_kernel at 1, 2, 4 and 8 blocks per CU):
-//   MC x MC      f16 nc 2 1.9 1.6 1.2 1.0, nc 3 1.4 0.7; f32 nc 2 2.7 1.7 1.1 1.2, nc 3
-//                1.9 1.0 0.8, nc 4 2.1 1.1 1.1 0.9; f64 nc 2 1.9 1.5 1.1 1.0, nc 3 1.7 1.1 0.9
-//   MC, plain    f16 nc 2 1.1 1.0 1.0, nc 3 1.3 1.1 1.0 0.9, nc 4 1.4 1.2 1.1 1.1; f32 nc 2
-//                1.6 1.3 1.1 1.2, nc 3 1.3 0.9 0.9; f64 nc 2 1.5 1.3 1.2 1.1, nc 3 1.4 1.2 1.1 1.0
-//   MC-Linear    f16 nc 2 1.8 1.6 1.3 1.1, nc 3 2.0 1.6 1.2 0.9; f32 nc 2 1.6 1.1 1.4 1.2, nc 3
-//                1.4 1.1 0.9; f64 nc 2 1.7 1.5 1.4 1.3, nc 3 1.7 1.4 1.3 1.1
-// binary64 nc = 4 with an MC A spills there.  With one component (no Simple-Renorm test, two
-// operations per step) seq_kernel's 16-byte LDS reads win on every grid: 4096^2 x 256 f16
-// 2.0, f32 2.9, f64 1.9.
-static int seq_blocks_per_cu(const MmLaunch &L) {
-  static constexpr int both[3][3] = {{4, 1, 1}, {8, 1, 2}, {4, 2, 0}};   // [f16, f32, f64][nc 2, 3, 4]
-  static constexpr int one_a[3][3] = {{2, 3, 8}, {8, 1, 8}, {8, 6, 0}};  // plain B
-  static constexpr int one_b[3][3] = {{2, 3, 8}, {8, 1, 8}, {8, 6, 3}};  // plain A
-  static constexpr int linear[3][3] = {{8, 4, 4}, {8, 2, 8}, {8, 8, 8}};
-  if (!L.a_mc && !L.b_mc) return 8;  // two plain factors
-  const auto &t = L.b_trans ? linear : (L.a_mc && L.b_mc ? both : (L.a_mc ? one_a : one_b));
-  return t[L.dtype][L.nc - 2];
+// how many half blocks of 256 outputs per CU it is the faster one, by kind, format, nc and
+// K (below 32, 64, 192 steps, and longer).  A short reduction has less of a chain to
+// overlap; one that is not a whole number of test groups runs zero steps at its end (they
+// fail the first test): it takes half the limit below 32 steps and for binary32 and binary64
+// the next shorter class's from there on (MC x MC: from 64 on).  Measured with both kernels at K = 16, 24, 48, 96, 256,
+// 768 and one more, on sizes that are and are not multiples of 16, from 1/4 to 8 blocks per
+// CU; a limit is the last size up to which no smaller one loses: seq_kernel's geometric
+// mean over a class is the better one and none of its sizes more than 7% slower.  Time of
+// mm_kernel over seq_kernel at 1, 2 and 4 blocks per CU, K = 48 | 256:
+//   MC x MC     f16 nc 2 1.43 1.25 0.98 | 1.38 1.14 0.81, nc 3 1.23 0.76 0.50 | 1.26 0.71 0.46
+//               f32 nc 2 1.52 1.23 0.95 | 2.05 1.49 1.13, nc 3 1.22 0.67 0.56 | 1.58 0.87 0.70
+//               f64 nc 2 1.57 1.23 0.97 | 1.74 1.32 1.07, nc 3 1.57 1.04 0.84 | 1.62 1.09 0.89
+//   MC, plain   f16 nc 2 0.95 0.92 0.94 | 1.08 0.99 0.96, nc 3 1.13 0.94 0.94 | 1.32 1.09 1.01
+//               f32 nc 2 1.07 1.12 1.11 | 1.45 1.45 1.23, nc 3 1.18 1.15 0.88 | 1.34 1.20 0.93
+//               f64 nc 2 1.25 1.19 1.14 | 1.31 1.24 1.17, nc 3 1.27 1.14 1.04 | 1.27 1.17 1.07
+//   plain, MC   f16 nc 2 0.95 0.91 0.93 |  -    -    -  , nc 3 1.05 0.97 0.92 | 1.39 1.19 1.04
+//               f32 nc 2 1.04 1.06 1.16 | 1.41 1.47 1.24, nc 3 1.31 1.19 0.93 | 1.28 1.27 0.98
+//               f64 nc 2 1.19 1.14 1.07 | 1.24 1.16 1.08, nc 3 1.37 1.17 1.02 | 1.41 1.12 1.01
+//   MC-Linear   f16 nc 2 1.24 1.25 1.21 | 1.62 1.44 1.27, nc 3 1.36 1.35 1.10 | 1.77 1.47 1.13
+//               f32 nc 2 1.06 1.12 1.22 | 1.54 1.57 1.32, nc 3 1.47 1.23 0.93 | 1.47 1.34 0.97
+//               f64 nc 2 1.34 1.29 1.25 | 1.44 1.36 1.29, nc 3 1.45 1.23 1.13 | 1.51 1.26 1.16
+//   plain dY    f16 nc 3 1.71 1.63 1.51 | 1.58 1.31 1.30, f32 nc 3 1.45 1.26 0.95 | 1.36 1.27 1.18,
+//               f64 nc 3 1.18 1.16 1.05 | 1.57 1.37 1.22
+// binary64 nc = 4 with an MC A spills.  binary32 nc = 4 with one MC operand sends its first
+// steps through the general algorithm (the fourth component that a binary64 value leaves
+// empty).  An MC dY (weight gradients, A stored [K][M]) has no staging launches with
+// seq_kernel: 1.08 at the least up to 8 blocks per CU.  With one component (no
+// Simple-Renorm test, two operations per step) its 16-byte LDS reads win on every grid:
+// 4096^2 x 256 f16 2.0, f32 2.9, f64 1.9.
+static int seq_half_blocks_per_cu(const MmLaunch &L) {
+  // [f16, f32, f64][nc 2, 3, 4][K < 32, < 64, < 192, longer]
+  using Table = uint8_t[3][3][4];
+  static constexpr Table both = {{{4, 6, 4, 4}, {2, 2, 2, 2}, {2, 2, 2, 2}},
+                                 {{4, 4, 8, 16}, {0, 2, 2, 2}, {2, 2, 4, 4}},
+                                 {{4, 6, 8, 8}, {2, 2, 4, 4}, {0, 0, 0, 0}}};
+  static constexpr Table one_a = {{{0, 0, 0, 4}, {0, 2, 2, 8}, {0, 2, 16, 16}},  // plain B
+                                  {{8, 8, 16, 16}, {3, 4, 6, 6}, {0, 0, 0, 16}},
+                                  {{8, 16, 16, 16}, {4, 8, 8, 8}, {0, 0, 0, 0}}};
+  static constexpr Table one_b = {{{0, 0, 0, 4}, {0, 2, 4, 8}, {0, 4, 16, 16}},  // plain A
+                                  {{8, 12, 16, 16}, {3, 4, 6, 6}, {0, 0, 0, 16}},
+                                  {{8, 8, 8, 12}, {4, 6, 6, 8}, {4, 4, 4, 4}}};
+  static constexpr Table linear = {{{8, 12, 12, 16}, {6, 8, 8, 8}, {4, 6, 6, 8}},
+                                   {{8, 16, 16, 16}, {4, 6, 6, 6}, {0, 0, 0, 16}},
+                                   {{16, 16, 16, 16}, {12, 16, 16, 16}, {4, 8, 8, 8}}};
+  static constexpr Table plain = {{{16, 16, 16, 16}, {16, 16, 16, 16}, {16, 16, 16, 16}},  // two plain factors
+                                  {{16, 16, 8, 16}, {6, 6, 8, 16}, {16, 16, 16, 16}},
+                                  {{16, 16, 16, 16}, {16, 8, 16, 16}, {16, 16, 16, 16}}};
+  if (L.a_trans && L.a_mc) return L.dtype == 2 && L.nc == 4 ? 0 : 16;
+  const bool mc_mc = L.a_mc && L.b_mc, f32_4 = L.dtype == 1 && L.nc == 4;
+  const auto &t = (L.b_trans ? linear : mc_mc ? both : L.a_mc ? one_a : L.b_mc ? one_b : plain)[L.dtype][L.nc - 2];
+  const int len = (L.K >= 32) + (L.K >= 64) + (L.K >= (f32_4 ? 128 : 192));
+  const bool ragged = L.K % (L.dtype == 2 || f32_4 ? 4 : 8) != 0;  // (seq_unroll)
+  if (!ragged || (mc_mc && len <= 1)) return t[len];
+  if (len == 0) return t[0] / 2;
+  return t[L.dtype == 0 || f32_4 ? len : len - 1];
 }
 
 bool seq_wanted(const MmLaunch &L) {
   if (L.prune) return false;
   if (L.nc == 1) return true;
-  // binary32 nc = 4, one MC operand: components that a binary64 value leaves empty send the
-  // first steps through the general algorithm (K = 64: 21 -> 24 us, K = 784: 276 -> 197 us)
-  if (L.K == 0 || (L.dtype == 1 && L.nc == 4 && !(L.a_mc && L.b_mc) && L.K < 128)) return false;
+  if (L.K == 0) return false;
   const int64_t blocks = ((L.M + 15) / 16) * ((L.N + 15) / 16);
-  return blocks <= (int64_t)256 * seq_blocks_per_cu(L) / (L.B1 * L.B2);
+  return blocks <= (int64_t)128 * seq_half_blocks_per_cu(L) / (L.B1 * L.B2);
 }
 
 hipError_t launch_seq(const MmLaunch &L, hipStream_t stream) {
