@@ -24,6 +24,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "mcf_arith.hpp"
 #include "mcf_internal.hpp"
 #include "mm_steps.hpp"
@@ -158,18 +160,28 @@ __device__ __forceinline__ bool seq_group(const SeqOps<T, NC, ROLE, U> &o, T (&a
   return low.zero();
 }
 
+// One step by the general algorithm.
+template <typename T, int NC, int ROLE>
+__device__ __forceinline__ void seq_general(const T (&x)[ROLE == SEQ_PLAIN ? 1 : NC], T v, T (&acc)[NC]) {
+  T t[NC], h[NC + 1];
+  seq_term_general<T, NC, ROLE>(x, v, t);
+  add_terms<T, NC>(acc, t, h);
+  compact_nz<T, NC + 1, NC>(h, acc);
+}
+
 // U steps into acc: the straight line, then the general algorithm for lanes that fail.
 // again(o2) reads the operands again (binary32 and binary64, for the strict test), from
 // somewhere the compiler cannot know, or it would keep the terms of the first attempt in
-// registers; one(u, x, v) reads those of step u.  valid: the lane's result is wanted;
-// first: these are the first steps of the reduction.
-// fails: the wavefront's state, how many of its groups failed the first test.  After two it
-// stays with the strict test, since what fails again is a property of its data; one alone
-// is a term that came out zero by chance, and a wavefront that left the first test for it
-// would be the slowest of the grid (256^2 x 256 binary32 nc = 3, plain A: 43 us when the
-// first failure counted, 31 us now).
-template <typename T, int NC, int ROLE, int U, typename Again, typename One>
-__device__ __forceinline__ void seq_steps(const SeqOps<T, NC, ROLE, U> &o, T (&acc)[NC], int &fails, bool valid,
+// registers; one(u, x, v) reads those of step u (HELD: the general algorithm takes the
+// group's operands from registers, where a read is a trip to memory).  valid: the lane's
+// result is wanted; first: these are the first steps of the reduction.
+// fails: the wavefront's state, how many of its groups failed the first test.  After LIMIT
+// it stays with the strict test: two, since what fails again is a property of its data, and
+// one alone is a term that came out zero by chance; a wavefront that left the first test
+// for it would be the slowest of the grid (256^2 x 256 binary32 nc = 3, plain A: 43 us when the
+// first failure counted, 31 us now).  With LIMIT = 1 a bool, tested as one: it stays a lane mask.
+template <typename T, int NC, int ROLE, int U, int LIMIT, bool HELD = false, typename Fails, typename Again, typename One>
+__device__ __forceinline__ void seq_steps(const SeqOps<T, NC, ROLE, U> &o, T (&acc)[NC], Fails &fails, bool valid,
                                           bool first, const Again &again, const One &one) {
   constexpr int NX = SeqOps<T, NC, ROLE, U>::NX;
   T saved[NC];
@@ -179,13 +191,16 @@ __device__ __forceinline__ void seq_steps(const SeqOps<T, NC, ROLE, U> &o, T (&a
   if constexpr (sizeof(T) == 2) {
     bad = seq_group<T, NC, ROLE, U, true>(o, acc);
   } else {
-    // (binary32 nc = 4: one failure, the fourth component that a binary64 value leaves empty)
-    if (fails < (sizeof(T) == 4 && NC == 4 ? 1 : 2)) {
+    if (LIMIT == 1 ? !fails : fails < LIMIT) {
       bad = seq_group<T, NC, ROLE, U, false>(o, acc);
       if (__builtin_expect(NC == 1 || !__any(bad && valid), 1)) return;
       // (not counted: the first steps of plain factors, whose accumulator has no third
       // component yet)
-      fails += ROLE != SEQ_PLAIN || !first;
+      const bool counted = ROLE != SEQ_PLAIN || !first;
+      if constexpr (LIMIT == 1)
+        fails = counted;
+      else
+        fails += counted;
 #pragma unroll
       for (int c = 0; c < NC; ++c) acc[c] = saved[c];
     }
@@ -196,13 +211,21 @@ __device__ __forceinline__ void seq_steps(const SeqOps<T, NC, ROLE, U> &o, T (&a
   if (NC > 1 && __builtin_expect(bad && valid, 0)) {
 #pragma unroll
     for (int c = 0; c < NC; ++c) acc[c] = saved[c];
+    if constexpr (HELD) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        T x[NX];
+#pragma unroll
+        for (int c = 0; c < NX; ++c) x[c] = o.x[c][u];
+        seq_general<T, NC, ROLE>(x, o.v[u], acc);
+      }
+    } else {
 #pragma unroll 1
-    for (int u = 0; u < U; ++u) {
-      T x[NX], v, t[NC], h[NC + 1];
-      one(u, x, v);
-      seq_term_general<T, NC, ROLE>(x, v, t);
-      add_terms<T, NC>(acc, t, h);
-      compact_nz<T, NC + 1, NC>(h, acc);
+      for (int u = 0; u < U; ++u) {
+        T x[NX], v;
+        one(u, x, v);
+        seq_general<T, NC, ROLE>(x, v, acc);
+      }
     }
   }
 }
@@ -363,7 +386,8 @@ seq_kernel(const SeqArgs<T> g) {
   }
   __syncthreads();
   int buf = 0;
-  int fails = 0;
+  constexpr int LIMIT = sizeof(T) == 4 && NC == 4 ? 1 : 2;  // (nc = 4: what fails first is an empty fourth component)
+  std::conditional_t<LIMIT == 1, bool, int> fails = 0;
   for (int64_t k0 = 0; k0 < K; k0 += KT, buf ^= 1) {
     const bool more = k0 + KT < K;
     if (more) fetch(k0 + KT);
@@ -377,7 +401,7 @@ seq_kernel(const SeqArgs<T> g) {
       seq_read<T, U>(at + vs, o.v);
     };
     auto steps = [&](const Ops &o, int kk) {
-      seq_steps<T, NC, ROLE, U>(
+      seq_steps<T, NC, ROLE, U, LIMIT>(
           o, acc, fails, valid, k0 + kk == 0,
           [&](Ops &o2) {
             int at = kk;

@@ -245,9 +245,11 @@ void sk_chain_kernel(const T *__restrict__ A, const T *__restrict__ B, T *__rest
         for (int c = 0; c < NC; ++c) ops.x[c][u] = x[c];
       }
     };
-    int fails = 0;
+    // (binary64: a count in place of a lane mask costs 256 x 1024 nc = 3, plain A 12.9 -> 14.2 us)
+    constexpr int LIMIT = sizeof(T) == 4 && NC <= 3 ? 2 : 1;
+    std::conditional_t<LIMIT == 1, bool, int> fails = 0;
     auto steps = [&](const Ops &ops, int64_t k) {
-      seq_steps<T, NC, ROLE, U>(
+      seq_steps<T, NC, ROLE, U, LIMIT, sizeof(T) == 2 && NC == 3>(
           ops, acc, fails, true, k == s,
           [&](Ops &o2) {
             int64_t at = k;
@@ -409,24 +411,35 @@ static void sk_reduce_launch(const T *W, T *C, int64_t MN, int G, hipStream_t s)
   hipLaunchKernelGGL((sk_reduce_kernel<T, NC, NP, APOL, R>), grid, dim3(SK_THREADS), 0, s, W, C, MN, G, GW);
 }
 
-// Blocks of 256 chains (one for each component of B when both operands are MC) up to which
+// Up to how many blocks of 256 chains (for each component of B when both operands are MC)
 // the chains' latency is what counts, and sk_chain_kernel the faster one; on larger grids
-// sk_kernel's higher occupancy keeps more loads in flight.  Matrix-vector products, us
-// with sk_kernel -> sk_chain_kernel:
-//   MC x MC    f32 nc 2: 500 blocks 19.3 -> 11.5, 512 15.8 -> 14.3, 1000 20.9 -> 23.1; nc 3:
-//              750 40.8 -> 37.6, 768 36.8 -> 32.7, 1500 40.0 -> 72.5; f64 nc 2: 512 19.9 -> 16.6,
-//              1000 25.3 -> 36.3; f16 nc 2: 500 21.4 -> 16.4, 4096 74.9 -> 64.1
-//   MC, plain  f32 nc 3: 125 blocks 21.7 -> 13.5, 250 22.0 -> 15.6, 256 16.0 -> 19.6; f64 nc 2: 250
-//              15.6 -> 13.6; f16 nc 2: 250 13.3 -> 15.6, nc 3: 500 26.5 -> 24.2
-//   plain, MC  f32 nc 3: 250 blocks 17.4 -> 12.5, 500 17.6 -> 14.2, 2048 42.8 -> 48.6; f64 nc 2: 500
-//              18.5 -> 16.8
-// nc = 1 (two operations a step) gains nothing; binary32 nc = 4 with one MC operand loses
-// (22.7 -> 33.1 us at 62 slices of 64 steps): the components beyond what a binary64 value
-// fills are zero or nearly, and its short slices start with many general steps.
-static bool sk_chain_wanted(int size, int nc, bool a_mc, bool b_mc, int64_t blocks) {
-  if (nc == 1 || (size == 4 && nc == 4 && !(a_mc && b_mc))) return false;
-  if (size == 2) return a_mc && b_mc ? blocks <= 4096 : (nc >= 3 && blocks <= 512);
-  return blocks <= (a_mc && b_mc ? 768 : (a_mc ? 255 : 512));
+// sk_kernel's higher occupancy keeps more loads in flight.  The block count alone separates
+// the two: matrix-vector products with 13 row counts from 1 to 6000 and 9 lengths from 512 to
+// 8192, each kernel's time at the last size below a limit and the first above (sk_kernel ->
+// sk_chain_kernel, us; in brackets the blocks):
+//   MC x MC    f32 nc 2 1536 x 4096 (384) 18.6 -> 15.8, 3000 x 2463 (750) 20.7 -> 26.5; nc 3
+//              880 x 4096 (220) 39.2 -> 34.4, 1536 x 2463 (384) 39.6 -> 61.9; nc 4 500 x 8192 (250)
+//              82 -> 52, 880 x 4321 (440) 85 -> 94; f64 nc 2 500 x 8192 (250) 20.5 -> 17.7,
+//              1536 x 2463 (384) 22.3 -> 29.3; nc 3 880 x 4096 (220) 47.9 -> 38.0, 1536 x 2463 58.1 -> 66.8
+//              f16 nc 2 6000 x 4096 (1500) 54 -> 47, nc 3 3000 x 8192 (1500) 137 -> 138
+//   MC, plain  f32 nc 3 500 x 8192 (250) 21.0 -> 14.1, 1536 x 4321 (768) 19.8 -> 24.4; f64 nc 3
+//              880 x 4096 (220) 20.3 -> 16.2, 1536 x 2463 (384) 23.5 -> 25.3
+//   plain, MC  f32 nc 3 880 x 4321 (440) 18.2 -> 16.5, 3000 x 2463 (750) 19.0 -> 21.1; f64 nc 3
+//              500 x 8192 (250) 19.2 -> 15.7, 1536 x 2463 (384) 23.0 -> 24.7
+// nc = 1 (two operations a step) gains nothing, nor does binary16 nc = 2 with one MC operand;
+// binary32 nc = 4 with one MC operand loses (22 -> 30 us at 16 slices of 64 steps): the
+// components beyond what a binary64 value fills are zero or nearly, and its short slices
+// start with many general steps.  And where a few of few slices have one step more than the
+// others' whole groups (binary32, one MC operand: 64 x 577, nc = 3, 9 slices 15.2 -> 17.3 us;
+// 64 x 576 14.7 -> 10.6, 64 x 608 15.3 -> 13.0), those lanes wait by themselves.
+static bool sk_chain_wanted(int size, int nc, bool a_mc, bool b_mc, int64_t blocks, int64_t K, int64_t S) {
+  const bool both = a_mc && b_mc;
+  if (nc == 1 || (size == 4 && nc == 4 && !both)) return false;
+  if (size == 2) return both ? blocks * nc <= 4096 : (nc >= 3 && blocks <= 512);
+  if (size == 8) return blocks <= 256;
+  if (both) return blocks <= (nc == 2 ? 384 : 256);
+  if (S <= 24 && K / S % 8 == 0 && K % S != 0 && 4 * (K % S) < S) return false;
+  return blocks <= (a_mc ? 256 : 512);
 }
 
 template <typename T, int NC, bool AMC, bool BMC>
@@ -442,7 +455,7 @@ static hipError_t sk_launch(int64_t M, int64_t N, int64_t K, const void *A, cons
   // S <= SPLITK_MAX_SLICES = 2^20 gives G <= 4096 = 16 x 256 group roots.
   if (G > 16 * SK_THREADS) return hipErrorInvalidValue;
   dim3 grid((unsigned)((MN + (SK_THREADS / KS) - 1) / (SK_THREADS / KS)), (unsigned)G);
-  if (sk_chain_wanted(sizeof(T), NC, AMC, BMC, (int64_t)grid.x * G * NP)) {
+  if (sk_chain_wanted(sizeof(T), NC, AMC, BMC, (int64_t)grid.x * G, K, S)) {
     constexpr int ROLE = AMC ? SEQ_AMC : SEQ_BMC;
     hipLaunchKernelGGL((sk_chain_kernel<T, NC, ROLE>), grid, dim3(SK_THREADS * NP), SK_THREADS * NP * NC * sizeof(T), s,
                        (const T *)A, (const T *)B, (T *)C, (T *)W, M, N, K, S, KS, G, NP, (const T *)nullptr, N);

@@ -198,3 +198,33 @@ def test_chain_kernel(mcf, orc, dt, nc, kinds):
             got = to_host(mcf.mc_matmul_splitk(to_dev(A), to_dev(B), nc=nc, a_mc=kinds[0], b_mc=kinds[1], slices=S))
             want = orc.matmul_splitk(A, B, nc=nc, slices=S, a_mc=kinds[0], b_mc=kinds[1])
             assert_bits(got, want, f"{dt.__name__} nc={nc} {kinds} {M}x{N}x{K} S={S} holes={holes}")
+
+
+LIMITS = [  # both sides of the block count up to which the chain kernel is taken
+    (np.float16, 2, (True, True), ((6000, 4096), (6000, 8192))),
+    (np.float16, 3, (True, False), ((880, 4096), (6000, 4096))),
+    (np.float32, 2, (True, True), ((1536, 4096), (3000, 2463))),
+    (np.float32, 3, (True, True), ((880, 4096), (1536, 2463))),
+    (np.float32, 3, (True, False), ((500, 8192), (1536, 4321))),
+    (np.float32, 3, (False, True), ((880, 4321), (3000, 2463))),
+    (np.float32, 3, (True, False), ((64, 576), (64, 577), (64, 608))),  # equal, few longer and many longer slices
+    (np.float64, 3, (True, False), ((880, 4096), (1536, 2463))),
+]
+
+
+@pytest.mark.parametrize("dt,nc,kinds,shapes", LIMITS)
+def test_around_the_chain_limit(mcf, orc, dt, nc, kinds, shapes):
+    """Matrix-vector products with the default slice counts on both sides of each limit, with
+    steps whose terms are zero (a wavefront counts them, or redoes them from registers)."""
+    g = np.random.default_rng(790 + nc)
+    for M, K in shapes:
+        A = inputs.expansion(g, (M, K), nc if kinds[0] else 1, dt, 0.3)
+        B = inputs.expansion(g, (K, 1), nc if kinds[1] else 1, dt, 0.3)
+        A[:, g.random((M, K)) < 0.002] = 0
+        A[-1][g.random((M, K)) < 0.002] = 0
+        got = to_host(mcf.mc_matmul_splitk(to_dev(A), to_dev(B), nc=nc, a_mc=kinds[0], b_mc=kinds[1]))
+        rows = np.concatenate([g.integers(0, M, 14), [0, M - 1]])
+        cols = np.zeros_like(rows)
+        want = orc.matmul_splitk(A, B, nc=nc, a_mc=kinds[0], b_mc=kinds[1],
+                                 slices=mcf.mc_matmul_splitk_slices(M, 1, K), rows=rows, cols=cols)
+        assert_bits(got[:, rows, cols], want, f"{dt.__name__} nc={nc} {kinds} {M}x{K}")
