@@ -9,7 +9,7 @@
 //     step has +0; that only changes zero signs of that Add-MCN's Two-Sum errors,
 //     which Simple-Renorm drops, and its outputs are the same;
 //   * the quotient digits share the reciprocal of the divisor's leading component
-//     (Divisor below);
+//     (Divisor below; not so Div-MCN of binary32);
 //   * the last quotient digit q_nc is computed only by lanes whose first digit is zero.
 //     The remainder is a Simple-Renorm output after the first update, so a later digit is
 //     zero only when the remainder is or when its quotient underflows, and then the update
@@ -27,6 +27,8 @@
 // patterns (a simulation of the binary16 nc = 3 workload found no other pattern in
 // more than 99.99% of the updates).
 #pragma once
+
+#include <type_traits>
 
 #include "mcf_arith.hpp"
 #include "mm_steps.hpp"
@@ -70,12 +72,18 @@ __device__ __forceinline__ void add_mcn_shift(const T (&x)[N], const T (&y)[N], 
   for (int i = 0; i < N; ++i) out[i] = z[0] ? h[i + 1] : h[i];
 }
 
-// Component divisions by one divisor.  General case: div_.
+// Component divisions by one divisor, each by itself.
 template <typename T>
-struct Divisor {
+struct IeeeDivisor {
   T y;
-  __device__ __forceinline__ explicit Divisor(T y0) : y(y0) {}
+  __device__ __forceinline__ explicit IeeeDivisor(T y0) : y(y0) {}
   __device__ __forceinline__ T divide(T a) const { return div_(a, y); }
+};
+
+// Component divisions that share the divisor's reciprocal.  General case: none.
+template <typename T>
+struct Divisor : IeeeDivisor<T> {
+  using IeeeDivisor<T>::IeeeDivisor;
 };
 
 // binary16 through binary32: q = a r with r within one unit in the last place of 1 / y,
@@ -101,11 +109,14 @@ struct Divisor<_Float16> {
   }
 };
 
-// binary32: the steps the compiler expands an IEEE division to (reciprocal, one Newton
-// step on it, quotient, two residual corrections), without its scaling, which leaves
-// operands in this range as they are: 2^-20 < |y| < 2^20, 2^-80 < |q| < 2^40 (so
+// binary32: the steps of LLVM's published lowering of an IEEE division for AMDGPU
+// (SITargetLowering::LowerFDIV32: reciprocal, one Newton step on it, quotient, two residual
+// corrections), without its scaling, which leaves operands in this range as they are: 2^-20 < |y| < 2^20, 2^-80 < |q| < 2^40 (so
 // |a| > 2^-100: every residual is exact).  Outside it, and for zero, infinite or NaN
-// operands, div_.
+// operands, div_.  For Mult-MCN and Mult-MCN-Slow, which their arithmetic bounds (2^24
+// elements, nc = 3 / 4: 141 / 252 us with divisions by themselves, 123 / 232 with this).
+// Div-MCN at those sizes is bound by memory, and a zero remainder sends its wavefront to
+// div_: EwDivisor.
 template <>
 struct Divisor<float> {
   float y, r;
@@ -125,13 +136,18 @@ struct Divisor<float> {
   }
 };
 
-template <typename T, int N>
+// What Div-MCN of binary32 takes, us with Divisor -> IeeeDivisor: 2^24 elements nc = 2 67.0 -> 66.1,
+// nc = 3 103.4 -> 101.4; 2^22 nc = 2 18.7 -> 18.0; 4096 to 2^16 nc = 4 9.4 .. 9.8 -> 8.6 .. 9.4.
+template <typename T>
+using EwDivisor = std::conditional_t<sizeof(T) == 4, IeeeDivisor<T>, Divisor<T>>;
+
+template <typename T, int N, typename D = Divisor<T>>
 __device__ __forceinline__ void div_mcn_fast(const T (&x_in)[N], const T (&y)[N], T (&out)[N]) {
   T x[N];
 #pragma unroll
   for (int c = 0; c < N; ++c) x[c] = x_in[c];
   T h[N + 1];
-  const Divisor<T> by(y[0]);
+  const D by(y[0]);
   T q = by.divide(x[0]);
   h[0] = q;
 #pragma unroll

@@ -91,7 +91,7 @@ __device__ __forceinline__ void elem(const T (&a)[NC], const T (&b)[NC], T (&r)[
     else
       scaling_n<T, NC, NC>(b, a[0], r);
   } else if constexpr (OP == EW_DIV) {
-    div_mcn_fast<T, NC>(a, b, r);
+    div_mcn_fast<T, NC, EwDivisor<T>>(a, b, r);
   } else if constexpr (OP == EW_EXP) {
     static_assert(sizeof(T) == 4, "binary16 Exp-MCN has its own kernel");
     T ex[NC];
