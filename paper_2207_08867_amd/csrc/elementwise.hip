@@ -206,6 +206,20 @@ constexpr int ew_width() {
   return 16 / (int)sizeof(T);
 }
 
+// Up to how many elements a long per-element algorithm takes one a lane although its
+// operands are aligned for ew_width: a lane's elements follow one another, and a small grid
+// is as slow as one lane.  Mult-MCN / Mult-MCN-Slow, us with 16 bytes a lane -> one element:
+//   binary32 nc = 3  2^16 12.0 -> 7.4 / 18.9 -> 6.2, 2^20 14.4 -> 10.6 / 21.0 -> 15.0, 2^22 36.1 -> 32.0 / 52.3
+//                    -> 45.4, 2^24 Mult-MCN 123 -> 125
+//   binary32 nc = 2  2^20 Mult-MCN-Slow 8.5 -> 6.1, 2^22 20.0 -> 20.0 / 20.6 -> 20.8, 2^24 Mult-MCN 69 -> 72
+//   binary16 nc = 2  2^16 10.3 -> 7.6 / 12.3 -> 6.2, 2^22 19.9 -> 16.1 / 24.3 -> 19.8, 2^24 Mult-MCN 54.6 -> 52.8
+// binary64 has two elements in 16 bytes.
+template <typename T, int NC, int OP, bool XMC, bool YMC>
+constexpr int64_t ew_narrow_limit() {
+  constexpr bool mult = OP == EW_MUL && XMC && YMC;
+  return sizeof(T) < 8 && NC >= 2 && (mult || OP == EW_MUL_SLOW) ? (int64_t)1 << 22 : 0;
+}
+
 template <typename T, int NC, int OP, bool XMC, bool YMC, int NCOUT>
 static hipError_t ew_launch(int64_t n, const void *x, const void *y, void *out, hipStream_t s) {
   constexpr int W = ew_width<T, NC, OP, XMC, YMC>();
@@ -216,7 +230,7 @@ static hipError_t ew_launch(int64_t n, const void *x, const void *y, void *out, 
   // vector access of VB bytes needs every plane start aligned to VB bytes
   bool vec = ((n * (int64_t)sizeof(T)) % VB == 0) && ((uintptr_t)x % VB == 0) &&
              (y == nullptr || (uintptr_t)y % VB == 0) && ((uintptr_t)out % VB == 0);
-  if (vec) {
+  if (vec && n > ew_narrow_limit<T, NC, OP, XMC, YMC>()) {
     hipLaunchKernelGGL((ew_kernel<T, NC, OP, XMC, YMC, NCOUT, W>), dim3(ew_blocks(n / W)), dim3(EW_THREADS), 0, s,
                        xp, yp, op, n);
   } else {

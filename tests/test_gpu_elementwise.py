@@ -333,3 +333,19 @@ def test_div_range_edges(mcf, orc, dt, nc, op):
         x[:, ::7] = y[:, ::7] * dt(1.5)  # exact first digits
     got = to_host(getattr(mcf, "mc_" + op)(to_dev(x), to_dev(y), nc=nc))
     assert_bits(got, getattr(orc, op)(x, y, nc=nc), f"{op} {dt.__name__} nc={nc}")
+
+
+@pytest.mark.parametrize("dt", [np.float16, np.float32])
+@pytest.mark.parametrize("nc", [2, 3, 4])
+@pytest.mark.parametrize("op", ["mul", "mul_slow"])
+def test_mult_widths(mcf, orc, dt, nc, op):
+    """Aligned operands on both sides of the size up to which a lane takes one element (2^22),
+    in full when small, otherwise both ends and a sample."""
+    for n in (8, 40_000, 1 << 22, (1 << 22) + 8):
+        x, y = _operands("mul", n, nc, dt, seed=130 + nc)
+        got = to_host(getattr(mcf, "mc_" + op)(to_dev(x), to_dev(y), nc=nc))
+        pick = np.r_[0:n]
+        if n > 40_000:
+            pick = np.r_[0:1000, np.random.default_rng(n).integers(0, n, 8000), n - 1000:n]
+        want = getattr(orc, op)(np.ascontiguousarray(x[:, pick]), np.ascontiguousarray(y[:, pick]), nc=nc)
+        assert_bits(got[:, pick], want, f"{op} {dt.__name__} nc={nc} n={n}")
