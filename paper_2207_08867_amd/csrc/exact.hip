@@ -77,8 +77,13 @@ constexpr int XSTAT_WORDS = XBADW + 64;
 // operand, B's words after A's, in the place of the slots.  MC-Linear nc = 3, us a call with
 // slots -> words: 16 x 64 x 64 18.7 -> 16.3, 64 x 512 x 512 28.9 -> 26.1, 1000 x 1024 x 1024 (2048
 // blocks) 46.0 -> 44.2; but 4096 x 1024 x 1024 (5120 blocks, read by 1024 workgroups) 95.9
-// -> 103.0.
+// -> 103.0.  Every product workgroup reads them all, so words times 64 x 64 output tiles is
+// limited too.  Over 130 sizes, nc = 2 .. 4, up to a product of 5120 x 256 the words were always
+// the faster ones, above 6144 x 256 never by 1%: 1500 x 512 x 1839 (1696 words, 696 tiles)
+// 68.5 -> 68.2, 2000 x 512 x 1839 (1952, 928) 73.7 -> 74.0, 3582 x 512 x 1024 (2304, 896) 68.7 -> 70.0,
+// 2750 x 512 x 1839 (2304, 1247) 128 -> 132.
 constexpr int64_t XBLOCK_WORDS = 2560;
+constexpr int64_t XBLOCK_READS = 5120 * 256;
 static_assert(XBLOCK_WORDS <= XSTAT_WORDS, "");
 
 // binary16 bits -> the exact integer value * 2^24 (finite inputs)
@@ -873,7 +878,8 @@ hipError_t launch_matmul_exact(int nc, int64_t M, int64_t N, int64_t K, const vo
   int8_t *DA = (int8_t *)(w + L.off_da), *DB = (int8_t *)(w + L.off_db);
 
   const int64_t a_words = L.Kp / XKSTEP * (L.Mp / 16), b_words = L.Kp / XKSTEP * (L.Np / 16);
-  uint32_t *words = a_words + b_words <= XBLOCK_WORDS ? stats : nullptr;
+  const int64_t all = a_words + b_words, tiles = (L.Mp / 64) * (L.Np / 64);
+  uint32_t *words = all <= XBLOCK_WORDS && all * tiles <= XBLOCK_READS ? stats : nullptr;
   if (words == nullptr) {
     const int64_t n = M > N ? M : N;
     const int64_t nb = (n > 4 * XSLOTS ? n : 4 * XSLOTS);
@@ -933,7 +939,6 @@ hipError_t launch_matmul_exact(int nc, int64_t M, int64_t N, int64_t K, const vo
   g.partial = (i128 *)(w + L.off_part);
   {
     g.tiles_n = L.Np / 64;
-    const int64_t tiles = (L.Mp / 64) * g.tiles_n;
     // fewer workgroups than two per compute unit: split each tile's k blocks over two
     // wavefronts per quarter
     if (tiles * L.Smax < 512)

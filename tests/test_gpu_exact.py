@@ -240,3 +240,17 @@ def test_exact_nonfinite_block_words(mcf, shape):
     for X, Y, what in ((bad_A, bad_B, "non-finite"), (A, B, "finite after it")):
         got = to_host(mcf.mc_matmul_exact(to_dev(X), to_dev(Y), nc=nc, workspace=ws))
         assert_bits(got[:, r, c], xp.matmul_exact(X, Y, nc=nc, rows=r, cols=c), f"{what} {shape}")
+
+
+@pytest.mark.parametrize("inp", [512, 576])
+def test_exact_block_word_reads(mcf, inp):
+    """Both sides of the limit on words times 64 x 64 tiles (1696 x 696 words, 1908 x 696 slots), with
+    a non-finite component in one row, at sampled outputs and along that row."""
+    nc, T, O = 3, 1500, 1839
+    X, W, b = next(inputs.linear_inputs(T, inp, O, nc, np.float16, seed=3300))
+    X[1203, inp - 1] = np.inf
+    got = to_host(mcf.mc_linear_fwd_exact(to_dev(X), to_dev(W), to_dev(b)))
+    r, c = sample_positions(T, O, 60, 3301)
+    r, c = np.r_[r, [1203] * 4, 1202, 1204], np.r_[c, 0, 63, 64, O - 1, 5, 5]
+    WT = np.ascontiguousarray(np.swapaxes(W, 1, 2))
+    assert_bits(got[:, r, c], xp.matmul_exact(X[None], WT, nc=nc, a_mc=False, bias=b, rows=r, cols=c), f"{inp}")
