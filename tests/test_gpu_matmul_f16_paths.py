@@ -3,10 +3,11 @@ kept-terms step, bitwise against the CPU oracle.
 
 The binary16 product computes only the terms Simple-Renorm keeps and proves per
 lane that the dropped final carry is zero (zeros form a trailing run and the last
-operation is exact, |result| < 2^-13); per tile it decides from the largest
-magnitude of each component plane whether the products of low components are
-exact, and whether A's components are in magnitude order.  These inputs make each of
-those decisions go both ways:
+operation is exact, |result| < 2^-13).  Products of these sizes run in the few-wavefront
+kernel, which tests each group of steps; the throughput kernel also decides per tile, from
+the largest magnitude of each component plane, whether the products of low components are
+exact, and whether A's components are in magnitude order: test_gpu_product_tiles.py runs it
+on the same inputs.  They make each of those decisions go both ways:
   * per-row and per-column scales spread over 2^-14 .. 2^2, so some tiles have
     exact low products and others do not, and the last-term test fails for some
     lanes and passes for others;
