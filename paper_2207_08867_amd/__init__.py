@@ -117,15 +117,17 @@ def _check(status: int, what: str):
 _DTYPE_CODES = {}
 _torch_module = None
 _raw_stream = None
+_plain_tensor = None
 
 
 def _torch():
-    global _torch_module, _raw_stream
+    global _torch_module, _raw_stream, _plain_tensor
     if _torch_module is None:
         import torch
 
         _DTYPE_CODES.update({torch.float16: MCF_F16, torch.float32: MCF_F32, torch.float64: MCF_F64})
         _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _plain_tensor = torch.Tensor
         _torch_module = torch
     return _torch_module
 
@@ -166,6 +168,13 @@ def _stream(t) -> int:
     return torch.cuda.current_stream(t.device).cuda_stream
 
 
+def _empty(x, shape):
+    """A result of x's type and device: a plain tensor also for operands of a Tensor subclass."""
+    if type(x) is _plain_tensor:
+        return x.new_empty(shape)
+    return _torch().empty(shape, dtype=x.dtype, device=x.device)
+
+
 def _same(x, y) -> bool:
     return x.dtype == y.dtype and x.get_device() == y.get_device()
 
@@ -193,7 +202,7 @@ def _binary(fn_name, x, y, nc, x_mc, y_mc, out, scaled=False):
         raise ValueError(f"shape mismatch: {sx} vs {sy}")
     n = math.prod(sx)
     if out is None:
-        out = x.new_empty((nc, *sx))
+        out = _empty(x, (nc, *sx))
     elif out.shape != (nc, *sx) or out.dtype != x.dtype:
         raise ValueError("out has the wrong shape or dtype")
     st = getattr(_lib or lib(), fn_name)(_code(x, scaled), nc, n, _dev(x, "x"), int(bool(x_mc)), _dev(y, "y"),
@@ -289,7 +298,7 @@ def _mm_operands(A, B, nc, a_mc, b_mc, out):
     if K != K2:
         raise ValueError(f"inner dimensions differ: {K} vs {K2}")
     if out is None:
-        out = A.new_empty((nc, M, N))
+        out = _empty(A, (nc, M, N))
     elif out.shape != (nc, M, N) or out.dtype != A.dtype:
         raise ValueError("out has the wrong shape or dtype")
     return A3, B3, M, N, K, out
@@ -439,7 +448,7 @@ def mc_linear_fwd_exact(x, W, b=None, *, out=None, workspace=None):
         raise ValueError("dtype or bias shape mismatch")
     T = x.shape[0]
     if out is None:
-        out = W.new_empty((nc, T, O))
+        out = _empty(W, (nc, T, O))
     elif tuple(out.shape) != (nc, T, O) or out.dtype != W.dtype:
         raise ValueError("out has the wrong shape or dtype")
     if workspace is None:
@@ -463,7 +472,7 @@ def mc_linear_fwd(x, W, b=None, *, out=None, scaled: bool = False):
         raise ValueError("dtype or bias shape mismatch")
     T = x.shape[0]
     if out is None:
-        out = W.new_empty((nc, T, O))
+        out = _empty(W, (nc, T, O))
     elif out.shape != (nc, T, O) or out.dtype != W.dtype:
         raise ValueError("out has the wrong shape or dtype")
     bp = _dev(b, "b") if b is not None else None
@@ -495,8 +504,8 @@ def mc_linear_bwd(x, W, dY, *, dy_mc: bool = True, dx: bool = True, dw: bool = T
     if x.dtype != W.dtype or dY.dtype != W.dtype:
         raise ValueError("dtype mismatch")
     code = _dtype_code(W)
-    outs = [W.new_empty((nc, T, I)) if dx else None, W.new_empty((nc, O, I)) if dw else None,
-            W.new_empty((nc, O)) if db else None]
+    outs = [_empty(W, (nc, T, I)) if dx else None, _empty(W, (nc, O, I)) if dw else None,
+            _empty(W, (nc, O)) if db else None]
     if (dw or db) and workspace is None:
         workspace = torch.empty(max(mc_linear_bwd_workspace(code, nc, T, I, O), 1), dtype=torch.uint8,
                                 device=W.device)

@@ -202,3 +202,20 @@ def test_linear_bwd_workspace(L):
     assert f(1, 2, 10, 0, 5) == a(2 * 5 * 10 * 4) + a(10 * 4) + a(2 * 5 * 4)
     assert f(0, 3, -1, 4, 4) == MCF_E_SHAPE
     assert f(7, 3, 4, 4, 4) == MCF_E_DTYPE
+
+
+def test_results_are_plain_tensors():
+    """The results that the binding makes have the operand's type and device, and are plain
+    tensors also when the operand is of a Tensor subclass."""
+    torch = pytest.importorskip("torch")
+    import paper_2207_08867_amd as m
+
+    class Sub(torch.Tensor):
+        pass
+
+    for x in (torch.zeros(2, 3), torch.zeros(2, 3, dtype=torch.float64), torch.zeros(2, 3).half().as_subclass(Sub),
+              torch.nn.Parameter(torch.zeros(2, 3))):
+        for _ in range(2):
+            out = m._empty(x, (2, 5, 4))
+            assert type(out) is torch.Tensor and out.shape == (2, 5, 4)
+            assert out.dtype == x.dtype and out.device == x.device and not out.requires_grad
