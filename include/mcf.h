@@ -325,9 +325,12 @@ int mc_linear_fwd(int dtype, int nc, int64_t batch, int64_t in, int64_t out, con
  * dX: [nc][batch][in], dW: [nc][out][in], db: [nc][out] -- each may be NULL (not
  * computed); outputs must not overlap the inputs, each other or the workspace.
  * workspace: device memory of at least mc_linear_bwd_workspace(...) bytes when dW or
- *   db is requested (dY^T staged in nc planes; then x with a column of ones appended and
- *   the [dW | db] product, which gives both in one pass), owned by the caller, not overlapping the inputs; contents on entry do not matter; calls sharing
- *   it must not overlap in time.  Too small: MCF_E_ARG; NULL when needed: MCF_E_NULL.
+ *   db is requested, owned by the caller, not overlapping the inputs; contents on entry do
+ *   not matter; calls sharing it must not overlap in time.  Too small: MCF_E_ARG; NULL when
+ *   needed: MCF_E_NULL.  The size covers every gradient and kind of dY: dY^T in nc planes,
+ *   then x with a column of ones appended and the [dW | db] product, which gives both in one
+ *   pass.  A call may touch less of it, or none: a plain dY stages one plane, and results of
+ *   few outputs (any size at nc = 1, and db alone) read dY and x as they are stored.
  * dtype: MCF_F16, MCF_F32, MCF_F64.  Sizes: batch, out <= 2^20, in <= 2^30 (and the
  * product limits of mc_matmul). */
 int mc_linear_bwd(int dtype, int nc, int64_t batch, int64_t in, int64_t out, const void *x, const void *W,

@@ -19,8 +19,9 @@
 // The step is launch- and latency-bound (three dependent launches for n <= 16447 and
 // d <= 16): 1 and 2 are one kernel with a sample a lane, 3 and 4 are one launch with every
 // sum's slices side by side (splitk.hip: sk_chain_kernel).  n = 10000, d = 2, a step of
-// binary32 nc = 2 / 3 and binary16 nc = 3: 39 / 58 / 84 us as five launches of the general
-// kernels, now 14 / 19 / 39 us.
+// binary32 nc = 2 / binary16 nc = 3: 39 / 84 us as five launches of the general kernels, now
+// 19.9 / 21.3 us (replayed from a graph 19.6 / 20.9; the kernels of the first take 2.9, 10.4
+// and 3.2 us).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

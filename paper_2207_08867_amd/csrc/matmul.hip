@@ -623,7 +623,8 @@ mm_kernel(const T *__restrict__ A, const T *__restrict__ B,
   // component plane.  The next tile's global loads are issued into registers before
   // the current tile's arithmetic, so their latency hides behind it; the registers
   // go to LDS at the top of the next iteration.  REPEAT: rows and columns past the edge
-  // repeat the last one (M <= 2^20, N <= 2^30 + 1), so that lanes outside the result take
+  // repeat the last one (M and N <= 2^30 + 1, so 32 bits hold an edge tile's rows: 2^20 rows from
+  // the products' own entries, 2^30 samples from the regression), so that lanes outside the result take
   // SR_FULL's common case like the others; zeros would send their wavefronts through the
   // general compaction at every step (16 x 500 x 50 x 200 binary32 nc = 3: 133 -> 81 us).
   // The kept-terms form accepts zeros, and the compares cost it registers.
@@ -949,7 +950,7 @@ static hipError_t mm_typed(const MmLaunch &L, hipStream_t s) {
 //   MC, plain   f16 nc 2 0.95 0.92 0.94 | 1.08 0.99 0.96, nc 3 1.13 0.94 0.94 | 1.32 1.09 1.01
 //               f32 nc 2 1.07 1.12 1.11 | 1.45 1.45 1.23, nc 3 1.18 1.15 0.88 | 1.34 1.20 0.93
 //               f64 nc 2 1.25 1.19 1.14 | 1.31 1.24 1.17, nc 3 1.27 1.14 1.04 | 1.27 1.17 1.07
-//   plain, MC   f16 nc 2 0.95 0.91 0.93 |  -    -    -  , nc 3 1.05 0.97 0.92 | 1.39 1.19 1.04
+//   plain, MC   f16 nc 2 0.95 0.91 0.93 | 1.10 1.00 0.95, nc 3 1.05 0.97 0.92 | 1.39 1.19 1.04
 //               f32 nc 2 1.04 1.06 1.16 | 1.41 1.47 1.24, nc 3 1.31 1.19 0.93 | 1.28 1.27 0.98
 //               f64 nc 2 1.19 1.14 1.07 | 1.24 1.16 1.08, nc 3 1.37 1.17 1.02 | 1.41 1.12 1.01
 //   MC-Linear   f16 nc 2 1.24 1.25 1.21 | 1.62 1.44 1.27, nc 3 1.36 1.35 1.10 | 1.77 1.47 1.13
