@@ -19,7 +19,7 @@
 //     last component infinite or NaN: such lanes take the full algorithm too;
 //   * the remainder updates x - y q compact their terms by a shift (add_mcn_shift).
 // Measured on 2^26 elements at nc = 3 against the literal algorithm: binary16 Div-MCN
-// 514 -> 215 us and Mult-MCN 986 -> 435 us; binary32 562 -> 424 and 1112 -> 500 us (at
+// 514 -> 207 us and Mult-MCN 986 -> 432 us; binary32 562 -> 418 and 1112 -> 500 us (at
 // about 5.5 TB/s; before the shared reciprocal, the digit test below and the short
 // Renormalize: 338, 734, 423 and 563 us).
 // The remainder updates x - y q cancel the leading component, so their terms usually
